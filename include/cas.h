@@ -112,8 +112,10 @@ cas_status cas_build_int8(cas_ctx* ctx);
  * calls.  Loading any tensor invalidates both copies. */
 cas_status cas_build_int4(cas_ctx* ctx);
 
-/* Commit n tokens as a causal sequence after the committed prefix (prefill),
- * in chunks of at most max_tree.  Leaves no round open. */
+/* Commit n tokens as a causal sequence after the committed prefix (prefill):
+ * up to 128 in chunks of at most max_tree, more in blocks of up to 2048 rows.
+ * The KV has the same bits either way.  Leaves no round open; the logits are
+ * those of the last (n - 1) % max_tree + 1 tokens. */
 cas_status cas_prefill(cas_ctx* ctx, const int32_t* tokens, int32_t n);
 
 /* Write committed KV of one layer directly (a cache restored from elsewhere):

@@ -23,7 +23,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libcas.so")
 LIB_DEBUG = os.path.join(PKG, "libcas_debug.so")
 RUNTIME_CHECK = os.path.join(PKG, "cas_runtime_check")
-SOURCES = ("kernels.hip", "runtime.hip")
+SOURCES = ("kernels.hip", "prefill.hip", "runtime.hip")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 CLANG = os.environ.get("CAS_CLANG", "/opt/rocm/llvm/bin/clang")
 ROCM_LIB = "/opt/rocm/lib"
@@ -63,7 +63,7 @@ def _link_lib(objs, out: str) -> None:
     os.replace(tmp, out)
 
 
-def _build_runtime_check(objdir: str, kernels_obj: str) -> str:
+def _build_runtime_check(objdir: str, kernel_objs) -> str:
     """csrc/runtime_check.c + runtime.hip (host code sanitized) + the release kernels."""
     rt = os.path.join(objdir, "runtime_hostsan.o")
     drv = os.path.join(objdir, "runtime_check.o")
@@ -71,20 +71,21 @@ def _build_runtime_check(objdir: str, kernels_obj: str) -> str:
     _run([CLANG, "-std=c11", "-O1", "-g", *C_SANITIZE, "-I" + INCLUDE, "-c", os.path.join(CSRC, "runtime_check.c"),
           "-o", drv], "compile of runtime_check.c")
     tmp = RUNTIME_CHECK + ".tmp"
-    _run([CLANG + "++", *C_SANITIZE, "-o", tmp, drv, rt, kernels_obj, "-L" + ROCM_LIB, "-lamdhip64",
+    _run([CLANG + "++", *C_SANITIZE, "-o", tmp, drv, rt, *kernel_objs, "-L" + ROCM_LIB, "-lamdhip64",
           "-Wl,-rpath," + ROCM_LIB], "link of cas_runtime_check")
     os.replace(tmp, RUNTIME_CHECK)
     return RUNTIME_CHECK
 
 
 def build_runtime_check(verbose: bool = False) -> str:
-    """Only the sanitized runtime check (needs the release kernels object of a
+    """Only the sanitized runtime check (needs the release kernel objects of a
     previous build())."""
     objdir = os.path.join(PKG, "_build")
-    kobj = os.path.join(objdir, "kernels.o")
-    if not os.path.exists(kobj):
-        raise RuntimeError(f"{kobj} is missing: run build() first")
-    out = _build_runtime_check(objdir, kobj)
+    kobjs = [os.path.join(objdir, k) for k in ("kernels.o", "prefill.o")]
+    for k in kobjs:
+        if not os.path.exists(k):
+            raise RuntimeError(f"{k} is missing: run build() first")
+    out = _build_runtime_check(objdir, kobjs)
     if verbose:
         print("built", out)
     return out
@@ -106,7 +107,7 @@ def build(verbose: bool = False) -> str:
     dbg = [os.path.join(objdir, s.replace(".hip", "_debug.o")) for s in SOURCES]
     _link_lib(rel, LIB)
     _link_lib(dbg, LIB_DEBUG)
-    _build_runtime_check(objdir, rel[0])
+    _build_runtime_check(objdir, rel[:-1])
     if verbose:
         print("built", LIB, LIB_DEBUG, RUNTIME_CHECK)
     return LIB

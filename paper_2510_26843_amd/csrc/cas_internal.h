@@ -26,8 +26,11 @@ __host__ __device__ inline int frag_elems(int et) { return et == ET_F32 ? 4 : (e
 __host__ __device__ inline int frag_elem_bytes(int et) { return et == ET_F32 ? 4 : (et == ET_BF16 ? 2 : 1); }
 __host__ __device__ inline int chunk_k(int et) { return 4 * FRAG_U * frag_elems(et); }
 __host__ __device__ inline int pad_k(int K, int et) { return (K + chunk_k(et) - 1) / chunk_k(et) * chunk_k(et); }
-// column tiles of the activation layout for T rows (the GEMM's NT)
-__host__ __device__ inline int col_tiles(int T) { return T <= 32 ? 2 : (T <= 64 ? 4 : 8); }
+// column tiles of the activation layout for T rows (the GEMM's NT); the many
+// rows of a prefill pad to whole 256-row blocks
+__host__ __device__ inline int col_tiles(int T) {
+    return T <= 32 ? 2 : (T <= 64 ? 4 : (T <= 128 ? 8 : (T + 255) / 256 * 16));
+}
 // element offset of W[n][k] (padded width Kp) and of X[t][k] (NT column tiles)
 __host__ __device__ inline size_t wt_off(int n, int k, int Kp, int E) {
     const int KC = 16 * E, c = k / KC, kk = k % KC;
@@ -201,6 +204,17 @@ bool gemm_qx_ok(int wtype, int N, int Kp, int T, int ksplit);
 // Whether a split-K GEMM can merge its input rows from attention partials.
 bool gemm_mx_ok(int wtype, int N, int Kp, int T, int ksplit);
 
+// Number of K ranges whose sums launch_gemm / launch_gemm_parts add up apart,
+// in order, for an N-row matrix (chunk boundaries floor(i C / R)): 1 where one
+// wave streams the whole K range, 4 for the short matrices whose four waves
+// split it, the split count for the split-K residual projections (resid).
+int gemm_sum_ranges(int wtype, int N, int Kp, int resid);
+// The linear layer of a prefill (129 or more rows; fp32 or bf16 weights,
+// EPI_STORE excluded): the sums are those of launch_gemm / launch_gemm_parts
+// with the same K ranges (a.ksplit of them, gemm_sum_ranges), bit for bit;
+// EPI_RESID adds them to the residual stream.
+hipError_t launch_gemm_rows(int wtype, int epi, const GemmArgs& a, hipStream_t s);
+
 struct AttnArgs {
     const void* q;        // [T][H][hd]
     const void* kc;       // key cache of the layer, Hkv blocks (cache layout)
@@ -234,6 +248,12 @@ int attention_splits_win(int Lc, int n_tree, int win_sink, int win_len);
 // atype: ET_BF16 (MFMA path, then the merge of the KV splits) or ET_F32
 // (plain path, ctx_cap <= 4096)
 hipError_t launch_attention(int atype, const AttnArgs& a, hipStream_t s);
+// The fp32 attention of both (causal: rows as of launch_attention_causal).
+hipError_t launch_attention_f32(const AttnArgs& a, int causal, hipStream_t s);
+// Causal attention of a prefill: row t sees slots [0, Lc + t].  The values
+// are those of launch_attention for the same rows, whatever the number of
+// rows (bf16: the same bits).  a.anc, the partials and the window are unused.
+hipError_t launch_attention_causal(int atype, const AttnArgs& a, hipStream_t s);
 // Only the merge of S split partials (a.part_o, a.part_ml; a.T rows of a.H
 // heads): bf16 rows into a.out, or with a.qout their codes and scales.
 hipError_t launch_attn_merge(const AttnArgs& a, int S, hipStream_t s);
@@ -286,6 +306,10 @@ hipError_t launch_untile_act(int atype, const void* src, int T, int K, void* dst
 hipError_t launch_embed(int atype, const void* embed, int d, int vocab, const int* round_tokens,
                         const int* round_parent, const StepParams* sp, int T, float* h, int* row_pos, int* row_slot,
                         uint64_t* row_anc, int* chk, hipStream_t s);
+// Embedding gather of a prefill's T rows: tokens tok [T] at slots and
+// positions sp->Lc + t.
+hipError_t launch_embed_chain(int atype, const void* embed, int d, int vocab, const int* tok, const StepParams* sp,
+                              int T, float* h, int* row_pos, int* row_slot, int* chk, hipStream_t s);
 // Greedy acceptance: per-row argmax of logits [T][V], then the tree walk.
 // result: [0] = n_accepted, [1] = bonus token, [2] = NaN flag, [3..] = node ids.
 hipError_t launch_accept(const float* logits, int T, int V, const int* round_tokens, const int* round_parent,

@@ -30,7 +30,13 @@ constexpr size_t kMaxGraphs = 64;   // captured forwards kept at once
 // gained on the 7B shape (12.6 -> 11.6 us) but lost on the 13B one (445 ->
 // 482 us per forward), and QKV and down lost 3-4%: they stay tile-major.
 constexpr int kProjKMajor[4] = {0, 0, 1, 0};
-constexpr size_t kStageBytes = 4096;
+// Rows a prefill runs through the layers at once: enough that the weights are
+// read seldom and the 256-row tiles fill the chip, at 0.3 GB of buffers for
+// the widest model shape.
+constexpr int kPrefillRows = 2048;
+// Longer prompts run as prefill blocks, shorter ones as tree chunks.
+constexpr int kPrefillTree = 128;
+constexpr size_t kStageBytes = 16 + 4 * (size_t)kPrefillRows;
 
 struct LayerW {
     void* wqkv = nullptr;   // [qkv_rows][d]: q heads, k heads (rows pair-interleaved), v heads
@@ -88,6 +94,8 @@ struct cas_ctx {
     int Lc = 0, n_nodes = 0, verified_n = 0, logits_rows = 0;
     std::vector<int> parent, token;
 
+    int pf_rows = 0;        // rows of the activation buffers (a prefill's; at least max_tree)
+    int* d_ptok = nullptr;  // tokens of a prefill's rows
     int* d_rtok = nullptr;
     int* d_rpar = nullptr;
     StepParams* d_sp = nullptr;
@@ -473,6 +481,97 @@ hipError_t enqueue_forward(cas_ctx* c, int T, const uint8_t* skip, int aq) {
     return hipSuccess;
 }
 
+// The launch sequence of one block of a prefill: T (more than 128) rows at the
+// slots from c->Lc on, causal.  A row's KV and hidden state have the bits of a
+// forward over a chain of the same tokens: the GEMMs add the same K ranges in
+// the same order and the attention merges the same splits.  logit_rows > 0:
+// the final norm and LM head of the last rows, as after such a forward.
+hipError_t enqueue_prefill(cas_ctx* c, int T, int logit_rows) {
+    const cas_config& f = c->cfg;
+    const int d = f.d_model, H = f.n_heads, Hkv = f.n_kv_heads, hd = f.head_dim, ffn = f.ffn_dim;
+    const int et = c->et;
+    hipStream_t s = c->stream;
+    hipError_t e;
+#define RUN(cls, call)                                        \
+    do {                                                      \
+        e = timed(c, (cls), [&]() -> hipError_t { return call; }); \
+        if (e != hipSuccess) return e;                        \
+    } while (0)
+    RUN(CAS_K_EMBED, launch_embed_chain(et, c->embed, d, f.vocab, c->d_ptok, c->d_sp, T, c->d_h, c->d_row_pos,
+                                        c->d_row_slot, c->d_chk, s));
+    const size_t kv_layer = (size_t)Hkv * c->ctx_cap * hd * c->es;
+    auto norm = [&](const float* gain) -> hipError_t {
+        return launch_rmsnorm(et, c->d_h, gain, T, d, f.rms_eps, c->d_xn, nullptr, nullptr, nullptr, 0, 0, 127, s);
+    };
+    auto gemm = [&](int epi, int which, const void* W, const void* X, int N, int Kp, GemmArgs g) -> hipError_t {
+        g.W = W;
+        g.X = X;
+        g.N = N;
+        g.Kp = Kp;
+        g.T = T;
+        g.chk = c->d_chk;
+        g.kmaj = kProjKMajor[which];
+        g.ksplit = gemm_sum_ranges(et, N, Kp, epi == EPI_RESID);
+        return launch_gemm_rows(et, epi, g, s);
+    };
+    for (int l = 0; l < f.n_layers; ++l) {
+        const LayerW& w = c->layers[l];
+        AttnArgs at{};
+        at.q = c->d_q;
+        at.kc = (char*)c->kc + kv_layer * l;
+        at.vt = (char*)c->vt + kv_layer * l;
+        at.sp = c->d_sp;
+        at.out = c->d_ao;
+        at.out_tiled = 1;
+        at.T = T;
+        at.H = H;
+        at.Hkv = Hkv;
+        at.hd = hd;
+        at.ctx_cap = c->ctx_cap;
+        at.chk = c->d_chk;
+        GemmArgs qkv{}, resid{}, gu{};
+        qkv.out = c->d_q;
+        qkv.rope_cos = c->rope_cos;
+        qkv.rope_sin = c->rope_sin;
+        qkv.row_pos = c->d_row_pos;
+        qkv.row_slot = c->d_row_slot;
+        qkv.kc = (void*)at.kc;
+        qkv.vt = (void*)at.vt;
+        qkv.H = H;
+        qkv.Hkv = Hkv;
+        qkv.hd = hd;
+        qkv.ctx_cap = c->ctx_cap;
+        resid.out = c->d_h;
+        resid.ldo = d;
+        gu.out = c->d_sw;
+        gu.ldo = ffn;
+        gu.out_k = ffn;
+        RUN(CAS_K_RMSNORM, norm(w.attn_norm));
+        RUN(CAS_K_GEMM_QKV, gemm(EPI_QKV, 0, w.wqkv, c->d_xn, c->qkv_rows, c->kp_d, qkv));
+        RUN(CAS_K_ATTN, launch_attention_causal(et, at, s));
+        RUN(CAS_K_GEMM_O, gemm(EPI_RESID, 1, w.wo, c->d_ao, d, c->kp_q, resid));
+        RUN(CAS_K_RMSNORM, norm(w.ffn_norm));
+        RUN(CAS_K_GEMM_GATEUP, gemm(EPI_SWIGLU, 2, w.wgu, c->d_xn, 2 * ffn, c->kp_d, gu));
+        RUN(CAS_K_GEMM_DOWN, gemm(EPI_RESID, 3, w.wd, c->d_sw, d, c->kp_f, resid));
+    }
+    if (logit_rows > 0) {
+        RUN(CAS_K_RMSNORM, launch_rmsnorm(et, c->d_h + (size_t)(T - logit_rows) * d, c->final_norm, logit_rows, d,
+                                          f.rms_eps, c->d_xn, nullptr, nullptr, nullptr, 0, 0, 127, s));
+        GemmArgs gh{};
+        gh.T = logit_rows;
+        gh.N = f.vocab;
+        gh.Kp = c->kp_d;
+        gh.W = c->lm_head;
+        gh.X = c->d_xn;
+        gh.out = c->d_logits;
+        gh.ldo = f.vocab;
+        gh.kmaj = 1;
+        RUN(CAS_K_GEMM_HEAD, launch_gemm(et, et, EPI_STORE, gh, s));
+    }
+#undef RUN
+    return hipSuccess;
+}
+
 std::string graph_key(const cas_ctx* c, int T, const uint8_t* skip, int aq, int S) {
     std::string k = std::to_string(T) + ":" + std::to_string(aq) + ":" + std::to_string(S) + ":" +
                     (c->gemv ? "g:" : "m:") +
@@ -593,6 +692,34 @@ cas_status do_forward(cas_ctx* c, const int32_t* tokens, const int32_t* parent, 
         HIPCHK(c, hipStreamSynchronize(c->stream));
         return poll_checks(c);
     }
+    return CAS_OK;
+}
+
+// Prefill of n (more than 128) tokens in equal blocks of at most pf_rows rows.
+// Afterwards the logits are those of the last tree-sized chunk's rows, as
+// after the chunk-wise prefill of shorter prompts.
+cas_status do_prefill_rows(cas_ctx* c, const int32_t* tokens, int n) {
+    cas_status st = check_ready(c, nullptr);
+    if (st != CAS_OK) return st;
+    const int blocks = (n + c->pf_rows - 1) / c->pf_rows, last = (n - 1) % c->cfg.max_tree + 1;
+    c->n_nodes = 0;
+    c->verified_n = 0;
+    for (int b = 0; b < blocks; ++b) {
+        const int t0 = (int)((long)n * b / blocks), t1 = (int)((long)n * (b + 1) / blocks), T = t1 - t0;
+        hipEvent_t ev = nullptr;
+        unsigned char* buf = next_stage(c, &ev);
+        if (!buf) return fail(c, CAS_ERR_DEVICE, "staging buffer wait failed");
+        StepParams sp{c->Lc, 0, T, c->chk_cap ? c->chk_cap : c->ctx_cap};
+        memcpy(buf, &sp, sizeof sp);
+        memcpy(buf + 16, tokens + t0, sizeof(int32_t) * T);
+        HIPCHK(c, hipMemcpyAsync(c->d_sp, buf, sizeof sp, hipMemcpyHostToDevice, c->stream));
+        HIPCHK(c, hipMemcpyAsync(c->d_ptok, buf + 16, 4 * (size_t)T, hipMemcpyHostToDevice, c->stream));
+        HIPCHK(c, hipEventRecord(ev, c->stream));
+        const hipError_t e = enqueue_prefill(c, T, b + 1 == blocks ? last : 0);
+        if (e != hipSuccess) return hip_fail(c, e, "prefill launch");
+        c->Lc += T;
+    }
+    c->logits_rows = last;
     return CAS_OK;
 }
 
@@ -769,24 +896,29 @@ cas_status cas_create(const cas_config* cfg, int device, void* stream, cas_ctx**
             hipMemcpy(c->rope_sin, sn.data(), sn.size() * 4, hipMemcpyHostToDevice) != hipSuccess)
             return cleanup(CAS_ERR_DEVICE, "RoPE table upload");
     }
+    // rows of the activation buffers: trees and prefill blocks; the tiled ones
+    // hold whole 128-row (trees) or 256-row (prefill) column tiles
+    const size_t P = c->pf_rows = std::max(f.max_tree, std::min(f.max_ctx, kPrefillRows));
+    const size_t PT = 16 * (size_t)std::max(8, col_tiles(c->pf_rows));
+    ALLOC(c->d_ptok, P * 4);
     ALLOC(c->d_rtok, T * 4);
     ALLOC(c->d_rpar, T * 4);
     ALLOC(c->d_sp, sizeof(StepParams));
     ALLOC(c->d_chk, 16);
     if (hipMemset(c->d_chk, 0, 16) != hipSuccess) return cleanup(CAS_ERR_DEVICE, "hipMemset of the check word");
-    ALLOC(c->d_row_pos, T * 4);
-    ALLOC(c->d_row_slot, T * 4);
+    ALLOC(c->d_row_pos, P * 4);
+    ALLOC(c->d_row_slot, P * 4);
     ALLOC(c->d_row_anc, T * 16);
-    ALLOC(c->d_h, T * d * 4);
-    // tiled activations hold 128 rows (8 column tiles) of the padded width
+    ALLOC(c->d_h, P * d * 4);
+    // tiled activations hold rows of the padded width
     const size_t kpmax = std::max(std::max(c->kp_d, c->kp_q), c->kp_f);
     const size_t kqmax = std::max(std::max(c->kq_d, c->kq_q), c->kq_f);
-    ALLOC(c->d_xn, 128 * kpmax * es);
+    ALLOC(c->d_xn, PT * kpmax * es);
     ALLOC(c->d_xq, 128 * kqmax);
     ALLOC(c->d_xs, T * 4);
-    ALLOC(c->d_q, T * c->qrows * es);
-    ALLOC(c->d_ao, 128 * (size_t)c->kp_q * es);
-    ALLOC(c->d_sw, 128 * (size_t)c->kp_f * es);
+    ALLOC(c->d_q, P * c->qrows * es);
+    ALLOC(c->d_ao, PT * (size_t)c->kp_q * es);
+    ALLOC(c->d_sw, PT * (size_t)c->kp_f * es);
     ALLOC(c->d_logits, T * (size_t)f.vocab * 4);
     c->part_bytes = attention_work_bytes(c->ctx_cap, (int)T, f.n_heads, f.head_dim);
     ALLOC(c->d_part, c->part_bytes);
@@ -949,6 +1081,7 @@ cas_status cas_prefill(cas_ctx* c, const int32_t* tokens, int32_t n) {
     if (c->Lc + n > c->cfg.max_ctx) return fail(c, CAS_ERR_CAPACITY, "prefill would exceed max_ctx");
     for (int i = 0; i < n; ++i)
         if (tokens[i] < 0 || tokens[i] >= c->cfg.vocab) return fail(c, CAS_ERR_ARG, "token out of range");
+    if (n > kPrefillTree) return do_prefill_rows(c, tokens, n);
     std::vector<int32_t> par(c->cfg.max_tree), acc(c->cfg.max_tree);
     for (int i = 0; i < c->cfg.max_tree; ++i) {
         par[i] = i - 1;

@@ -1,0 +1,77 @@
+"""Prefill of prompts longer than a tree against the same tokens committed
+chunk by chunk through the verify forward (a chain of up to 128 nodes): the
+committed KV of every layer, the logits the prefill leaves behind and the
+next forward's logits hold the same bits, whatever the block and tile edges."""
+import numpy as np
+import pytest
+
+from paper_2510_26843_amd import cas, synth
+
+pytestmark = pytest.mark.gpu
+
+S = synth.ModelShape
+SHAPES = {
+    # fp32; head width 64
+    "f32": S("f32", 2, 256, 4, 4, 64, 688, 512, 1e4, 1e-6, "f32"),
+    # bf16 grouped query, every matrix short: four K ranges (QKV, gate/up), 2 and 5 split-K sums, pad columns
+    "gqa": S("gqa", 2, 512, 8, 2, 64, 1376, 512, 5e5, 1e-6, "bf16"),
+    # head width 128; gate/up tall (one K range) with a tile count off the block edges; fewer chunks than ranges
+    "tall": S("tall", 2, 256, 4, 2, 128, 4416, 512, 1e4, 1e-6, "bf16"),
+    # tall QKV, rows of more than one block's tiles
+    "mha": S("mha", 1, 1024, 24, 24, 128, 4448, 512, 1e4, 1e-6, "bf16"),
+}
+
+
+def _model(shape, w, max_ctx):
+    m = cas.Model(shape, max_ctx=max_ctx, max_tree=128)
+    m.load_weights(w)
+    return m
+
+
+def _chunks(m, toks):
+    for i in range(0, len(toks), 128):
+        part = toks[i:i + 128]
+        lg = m.forward(part, list(range(-1, len(part) - 1)))
+        m.compact(list(range(len(part))))
+    return lg
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+@pytest.mark.parametrize("head,n", [(0, 129), (0, 256), (37, 411), (0, 1025), (100, 2300)])
+def test_long_prefill_matches_tree_chunks(name, head, n):
+    shape = SHAPES[name]
+    w = synth.gen_weights(shape, seed=3)
+    toks = [int(x) for x in synth.gen_prompt(shape.vocab, head + n, seed=n)]
+    ref, got = _model(shape, w, head + n + 128), _model(shape, w, head + n + 128)
+    for m in (ref, got):
+        if head:
+            m.prefill(toks[:head])
+    lg = _chunks(ref, toks[head:])
+    got.prefill(toks[head:])
+    assert got.committed == ref.committed == head + n
+    ids, probs = got.topk(4, len(lg))  # the last chunk's logits stay readable
+    order = np.argsort(-lg, axis=1, kind="stable")[:, :4]
+    assert np.array_equal(ids, order)
+    for l in range(shape.n_layers):
+        for a, b in zip(got.kv_read(l, head + n), ref.kv_read(l, head + n)):
+            assert np.array_equal(a, b), (l, np.argwhere(a != b)[:4])
+    tree = synth.tree_from_branching(*synth.TREE_TINY)
+    tt = synth.gen_tree_tokens(tree, shape.vocab, seed=9)
+    assert np.array_equal(got.forward(tt, tree), ref.forward(tt, tree))
+    ref.close()
+    got.close()
+
+
+def test_long_prefill_refuses_what_it_refused():
+    shape = SHAPES["f32"]
+    m = cas.Model(shape, max_ctx=512, max_tree=64)
+    with pytest.raises(cas.CasError):
+        m.prefill([1] * 300)  # nothing loaded
+    m.load_weights(synth.gen_weights(shape, seed=3))
+    for bad in ([1] * 513, [1] * 200 + [shape.vocab], [-1] + [1] * 200):
+        with pytest.raises(cas.CasError):
+            m.prefill(bad)
+        assert m.committed == 0
+    m.prefill([1] * 300)
+    assert m.committed == 300
+    m.close()
