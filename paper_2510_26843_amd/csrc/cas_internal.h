@@ -209,11 +209,14 @@ bool gemm_mx_ok(int wtype, int N, int Kp, int T, int ksplit);
 // wave streams the whole K range, 4 for the short matrices whose four waves
 // split it, the split count for the split-K residual projections (resid).
 int gemm_sum_ranges(int wtype, int N, int Kp, int resid);
-// The linear layer of a prefill (129 or more rows; fp32 or bf16 weights,
-// EPI_STORE excluded): the sums are those of launch_gemm / launch_gemm_parts
-// with the same K ranges (a.ksplit of them, gemm_sum_ranges), bit for bit;
-// EPI_RESID adds them to the residual stream.
+// The linear layer of a prefill (129 or more rows; fp32 or bf16 weights): the
+// sums are those of launch_gemm / launch_gemm_parts with the same K ranges
+// (a.ksplit of them, gemm_sum_ranges), bit for bit; EPI_RESID adds them to the
+// residual stream, EPI_STORE (where gemm_rows_split says so) leaves each
+// range's sums at a.out + k * a.part_stride, as launch_gemm_parts does.
 hipError_t launch_gemm_rows(int wtype, int epi, const GemmArgs& a, hipStream_t s);
+constexpr int PF_SPLIT_ROWS = 512;  // most rows of a prefill with split partial sums
+bool gemm_rows_split(int wtype, int N, int Kp, int T);
 
 struct AttnArgs {
     const void* q;        // [T][H][hd]

@@ -193,13 +193,6 @@ __device__ __forceinline__ void mfma_result_pad() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// A wave's 1 KB (16 bytes per lane) from global memory straight to LDS:
-// lane l's bytes land at dst + 16 l.
-__device__ __forceinline__ void lds_load16(const void* src, void* dst) {
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                     (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
-}
-
 template <int WT>
 __device__ __forceinline__ typename WTr<WT>::acc_t mfma_step(i32x4 a, i32x4 b, typename WTr<WT>::acc_t c) {
     if constexpr (WT == ET_BF16) {

@@ -7,37 +7,53 @@ namespace cas {
 
 // ---------------------------------------------------------------- GEMM of many rows
 
+// Direct-to-LDS load of one wave: 16 bytes per lane from base + voff (base
+// uniform, voff per lane) to LDS byte lds + 16 lane.  Written out because the
+// compiler, which cannot tell the ring's stages apart, would wait for every
+// load in flight before each LDS read; stage_wait() below is the wait.  (No
+// register is written; s_nop: the wait state between m0 and its use.)
+__device__ __forceinline__ void lds_load16(const char* base, uint32_t voff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds)
+                 : "memory");
+}
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
+}
+// All but the last N of this wave's direct-to-LDS loads have landed and its
+// LDS reads are done; then the same holds for every wave of the workgroup.
+template <int N>
+__device__ __forceinline__ void stage_wait() {
+    static_assert(N >= 0 && N <= 63, "vmcnt");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
 // Prefill: the same linear layers over hundreds to thousands of rows, where
 // the weights are reused and the matrix cores are what counts.  A workgroup
 // computes (16 NW WN) weight rows x (16 TW WT_) activation rows; its WN x WT_
 // waves own NW x TW MFMA tiles each.  Both operands lie in memory as 1 KB
-// fragments, so a stage (two k-steps of every tile) goes to LDS with
-// direct-to-LDS loads, 1 KB per wave instruction, and every MFMA operand is
-// one conflict-free 16-byte LDS read; no register passes through, no swizzle.
-// Two stages alternate: the next one's loads are in flight while the current
-// one is multiplied, and __syncthreads() both waits for them and frees the
-// buffer (four separate arrays, so that the reads of one stage do not wait
-// for the loads of the other).
+// fragments, so a k-step of every tile goes to LDS with direct-to-LDS loads,
+// 1 KB per wave instruction, and every MFMA operand is one conflict-free
+// 16-byte LDS read; no register passes through, no swizzle.  D one-step
+// stages form a ring: while step s is multiplied out of registers, the
+// fragments of s + 1 are read into the other register set and the loads of
+// s + 2 .. s + D are in flight; one barrier per step.
 //
 // The k order of a sum is that of k_gemm / k_gemm_wide: the same MFMA, steps
 // in order; where those split K over waves or workgroups (RNG: a.ksplit
-// ranges) each range is summed from zero and added to the total in order.  A
-// row's result therefore has the same bits in a prefill, a verify and a
-// one-row call.
-//
-// Measured, prefill of 1024 tokens on the 7B shapes (blocks of 256 x 256,
-// or 128 x 128 with ranges): QKV 139 us, gate/up 229 us (805 TFLOP/s), O 64,
-// down 157; before, eight passes of the weight-streaming kernels at 128 rows
-// took 8 x (43, 45, 15, 30) us, and each pass its own LM head.
-template <int WT, int NW, int TW, int WN, int WT_, int EPI, typename AT, bool KM, bool RNG>
-__global__ void __launch_bounds__(64 * WN * WT_, 2) k_gemm_rows(const GemmArgs a) {
+// ranges) each range is summed from zero and added to the total in order, or,
+// with few workgroups, computed by a workgroup of its own (SPL: gridDim.y =
+// a.ksplit, range k's sums stored at a.out + k * a.part_stride for the next
+// norm to add).  A row's result therefore has the same bits in a prefill, a
+// verify and a one-row call.
+template <int WT, int NW, int TW, int WN, int WT_, int D, int EPI, typename AT, bool KM, bool RNG, bool SPL>
+__global__ void __launch_bounds__(64 * WN * WT_, 2) k_gemm_rows(GemmArgs a) {
     using ACC = typename WTr<WT>::acc_t;
-    constexpr int E = WTr<WT>::E, W = WN * WT_, BN = NW * WN, BT = TW * WT_, US = 2;
-    constexpr int LA = BN * US / W, LB = BT * US / W;  // 1 KB loads per wave and stage
-    static_assert(!is_int<WT>(), "fp32 and bf16 weights");
-    static_assert(LA * W == BN * US && LB * W == BT * US && FRAG_U == 2 * US, "stage shape");
-    __shared__ __attribute__((aligned(16))) char sa0[BN * US * 1024], sb0[BT * US * 1024];
-    __shared__ __attribute__((aligned(16))) char sa1[BN * US * 1024], sb1[BT * US * 1024];
+    constexpr int E = WTr<WT>::E, W = WN * WT_, BN = NW * WN, BT = TW * WT_;
+    constexpr int LA = BN / W, LB = BT / W, LD = LA + LB;  // 1 KB loads per wave and step
+    constexpr int SB = (BN + BT) * 1024;                   // bytes of a stage
+    static_assert(!is_int<WT>() && !(RNG && SPL), "fp32 and bf16 weights; one way with the ranges");
+    static_assert(LA * W == BN && LB * W == BT && D % FRAG_U == 0, "stage shape");
+    __shared__ __attribute__((aligned(16))) char sm[D * SB];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wn = wave / WT_, wt = wave % WT_;
@@ -49,22 +65,41 @@ __global__ void __launch_bounds__(64 * WN * WT_, 2) k_gemm_rows(const GemmArgs a
     const int xcd = blockIdx.x % 8, per = nb / 8, rem = nb % 8;
     const int lin = xcd * per + min(xcd, rem) + blockIdx.x / 8;
     const int tn0 = (lin / nT) * BN, tt0 = (lin % nT) * BT;  // first weight / row tile
-    const int C = a.Kp / (16 * E), NS = 2 * C;               // chunks, stages
+    const int CW = a.Kp / (16 * E);                          // chunks of the matrix
+    const int c0 = SPL ? (int)(((long)blockIdx.y * CW) / gridDim.y) : 0;
+    const int C = SPL ? (int)(((long)(blockIdx.y + 1) * CW) / gridDim.y) - c0 : CW;  // chunks of this workgroup
+    const int NS = C * FRAG_U;                                                       // steps
+    if constexpr (SPL) a.out = (float*)a.out + blockIdx.y * a.part_stride;
 
-    // 1 KB blocks of this wave: block i of a stage is step i / BN of tile i % BN
+    // 1 KB blocks of this wave: LA weight tiles, LB row tiles of each step
     const size_t ast = (KM ? (size_t)ntiles : 1) * 1024, bst = (size_t)nto * 1024;  // bytes per step
     const char* pa[LA];
     const char* pb[LB];
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
-        const int b = wave * LA + i, tile = min(tn0 + b % BN, ntiles - 1);
-        pa[i] = (const char*)a.W + (KM ? (size_t)tile : (size_t)tile * C * FRAG_U) * 1024 + (b / BN) * ast + lane * 16;
+        const int tile = min(tn0 + wave * LA + i, ntiles - 1);
+        pa[i] = (const char*)a.W + (KM ? (size_t)tile : (size_t)tile * CW * FRAG_U) * 1024 + c0 * FRAG_U * ast;
     }
 #pragma unroll
-    for (int i = 0; i < LB; ++i) {
-        const int b = wave * LB + i, tile = min(tt0 + b % BT, nto - 1);
-        pb[i] = (const char*)a.X + (size_t)tile * 1024 + (b / BT) * bst + lane * 16;
-    }
+    for (int i = 0; i < LB; ++i)
+        pb[i] = (const char*)a.X + (size_t)min(tt0 + wave * LB + i, nto - 1) * 1024 + c0 * FRAG_U * bst;
+    const uint32_t vo = lane * 16;
+    const uint32_t la = lds_addr(sm) + wave * LA * 1024, lb = lds_addr(sm) + (BN + wave * LB) * 1024;
+    // the next step's loads; past the last step the pointers stay (a reload
+    // into a stage that is not read again), so that the counts of loads in
+    // flight hold to the end
+    auto load = [&](int stg, bool more) {
+#pragma unroll
+        for (int i = 0; i < LA; ++i) {
+            lds_load16(pa[i], vo, la + stg * SB + i * 1024);
+            pa[i] += more ? ast : 0;
+        }
+#pragma unroll
+        for (int i = 0; i < LB; ++i) {
+            lds_load16(pb[i], vo, lb + stg * SB + i * 1024);
+            pb[i] += more ? bst : 0;
+        }
+    };
     ACC acc[NW][TW], tot[RNG ? NW : 1][RNG ? TW : 1];
 #pragma unroll
     for (int i = 0; i < NW; ++i)
@@ -73,56 +108,65 @@ __global__ void __launch_bounds__(64 * WN * WT_, 2) k_gemm_rows(const GemmArgs a
             acc[i][j] = ACC{0, 0, 0, 0};
             if constexpr (RNG) tot[i][j] = ACC{0, 0, 0, 0};
         }
-    auto stage = [&](char* sa, char* sb, int s) {
+    i32x4 A[2][NW], B[2][TW];
+    auto read = [&](int p, int stg) {
+        const char* sb = sm + stg * SB;
 #pragma unroll
-        for (int i = 0; i < LA; ++i) lds_load16(pa[i] + (size_t)s * US * ast, sa + (wave * LA + i) * 1024);
+        for (int i = 0; i < NW; ++i) A[p][i] = *(const i32x4*)(sb + (wn * NW + i) * 1024 + lane * 16);
 #pragma unroll
-        for (int i = 0; i < LB; ++i) lds_load16(pb[i] + (size_t)s * US * bst, sb + (wave * LB + i) * 1024);
-        __builtin_amdgcn_sched_barrier(0);  // the loads go first, not behind the LDS reads
+        for (int j = 0; j < TW; ++j) B[p][j] = *(const i32x4*)(sb + (BN + wt * TW + j) * 1024 + lane * 16);
     };
-    auto mma = [&](const char* sa, const char* sb) {
-#pragma unroll
-        for (int u = 0; u < US; ++u) {
-            i32x4 A[NW], B[TW];
-#pragma unroll
-            for (int i = 0; i < NW; ++i) A[i] = *(const i32x4*)(sa + (u * BN + wn * NW + i) * 1024 + lane * 16);
-#pragma unroll
-            for (int j = 0; j < TW; ++j) B[j] = *(const i32x4*)(sb + (u * BT + wt * TW + j) * 1024 + lane * 16);
-#pragma unroll
-            for (int i = 0; i < NW; ++i)
-#pragma unroll
-                for (int j = 0; j < TW; ++j) acc[i][j] = mfma_step<WT>(A[i], B[j], acc[i][j]);
-        }
-    };
-    // first chunk of the next range with any (K shorter than ksplit chunks leaves some empty)
+    // end of the first K range with any chunk (K shorter than ksplit chunks leaves some empty)
     int range = 0, bound = 0;
     auto next_bound = [&](int c) {
         while (bound <= c && range < a.ksplit) bound = (int)(((long)++range * C) / a.ksplit);
     };
     if constexpr (RNG) next_bound(0);
-    stage(sa0, sb0, 0);
-    __syncthreads();
-    for (int c = 0; c < C; ++c) {
-        stage(sa1, sb1, 2 * c + 1);
-        mma(sa0, sb0);
-        __syncthreads();
-        if (c + 1 < C) stage(sa0, sb0, 2 * c + 2);
-        mma(sa1, sb1);
-        if constexpr (RNG) {
-            if (c + 1 == bound) {
-                mfma_result_pad();
 #pragma unroll
-                for (int i = 0; i < NW; ++i)
+    for (int q = 0; q < D; ++q) load(q, q + 1 < NS);
+    stage_wait<(D - 1) * LD>();
+    read(0, 0);
+    for (int s0 = 0; s0 < NS; s0 += D) {
 #pragma unroll
-                    for (int j = 0; j < TW; ++j) {
-                        tot[i][j] += acc[i][j];
-                        acc[i][j] = ACC{0, 0, 0, 0};
-                    }
-                next_bound(c + 1);
+        for (int q = 0; q < D; ++q) {
+            const int s = s0 + q, p = q & 1;
+            if (D > FRAG_U && q % FRAG_U == 0 && s >= NS) break;
+            // stage q is read by every wave, stage q + 1 has landed
+            stage_wait<(D - 2) * LD>();
+            load(q, s + D + 1 < NS);
+            __builtin_amdgcn_sched_barrier(0);  // the loads go first, not behind the LDS reads
+            read(p ^ 1, (q + 1) % D);
+#pragma unroll
+            for (int i = 0; i < NW; ++i)
+#pragma unroll
+                for (int j = 0; j < TW; ++j) acc[i][j] = mfma_step<WT>(A[p][i], B[p][j], acc[i][j]);
+            if constexpr (NW * TW == 32) {
+                // two MFMAs per LDS read (left to itself the compiler puts the
+                // reads in front): 256 x 256 blocks 201 -> 193 us for the 7B
+                // gate/up at 1024 rows; 128 x 128 blocks were slower this way
+#pragma unroll
+                for (int k = 0; k < NW + TW; ++k) {
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x8, 2, 0);
+                }
+            }
+            if constexpr (RNG) {
+                if (q % FRAG_U == FRAG_U - 1 && s / FRAG_U + 1 == bound) {
+                    mfma_result_pad();
+#pragma unroll
+                    for (int i = 0; i < NW; ++i)
+#pragma unroll
+                        for (int j = 0; j < TW; ++j) {
+                            tot[i][j] += acc[i][j];
+                            acc[i][j] = ACC{0, 0, 0, 0};
+                        }
+                    next_bound(bound);
+                }
             }
         }
-        __syncthreads();
+        asm volatile("" ::: "memory");  // the last step's reads stay before the next round's barrier
     }
+    stage_wait<0>();
     mfma_result_pad();
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
@@ -144,23 +188,54 @@ int gemm_sum_ranges(int wtype, int N, int Kp, int resid) {
     return N >= 8192 && ((N / 16) % 4 == 0 || (N / 16) % 3 == 0) ? 1 : 4;
 }
 
-template <int WT, int NW, int TW, int WN, int WT_, int EPI, typename AT, bool KM, bool RNG>
+template <int WT, int NW, int TW, int WN, int WT_, int EPI, typename AT, bool KM, bool RNG, bool SPL = false>
 static hipError_t gemm_rows_launch(const GemmArgs& a, hipStream_t s) {
     const int nT = ((a.T + 15) / 16 + TW * WT_ - 1) / (TW * WT_), nN = (a.N / 16 + NW * WN - 1) / (NW * WN);
-    hipLaunchKernelGGL((k_gemm_rows<WT, NW, TW, WN, WT_, EPI, AT, KM, RNG>), dim3(nT * nN), dim3(64 * WN * WT_), 0, s, a);
+    hipLaunchKernelGGL((k_gemm_rows<WT, NW, TW, WN, WT_, 4, EPI, AT, KM, RNG, SPL>), dim3(nT * nN, SPL ? a.ksplit : 1),
+                       dim3(64 * WN * WT_), 0, s, a);
     return hipGetLastError();
 }
 
+// Blocks of 128 x 128 as eight waves of 32 x 64 (64 KB: two workgroups per CU),
+// 128 x 256 as eight of 64 x 64, or 256 x 256 as eight of 128 x 64.  The larger
+// ones read less LDS per MFMA but come one per CU: measured at K = 4096, a CU's
+// first 128 x 128 block takes 40 us and each further one 32-36, a round of
+// 128 x 256 blocks 57-65 us, one of 256 x 256 blocks 90-105.  The block with
+// the least cost in these units is taken: 1024 rows of the 7B QKV 95 / 115 /
+// 101 us, gate/up 200 / 194 / 201, down 88 / 130 / 206; 2048 rows of the 8B
+// gate/up 537 / 497 / 453; 1504 rows of its down projection 188 / 172 / 273.
+// (Eight waves and not four for 128 x 128: 7B down 88 against 96 us; rings of
+// eight stages were slower, 113 us.)
 template <int WT, int EPI, typename AT, bool KM>
 static hipError_t gemm_rows_go(const GemmArgs& a, hipStream_t s) {
     if (a.kmaj != (int)KM) return hipErrorInvalidValue;
-    if (a.ksplit > 1) return gemm_rows_launch<WT, 4, 4, 2, 2, EPI, AT, KM, true>(a, s);
-    return gemm_rows_launch<WT, 8, 4, 2, 4, EPI, AT, KM, false>(a, s);
+    const int tt = (a.T + 15) / 16, tn = a.N / 16;
+    auto blocks = [&](int bn, int bt) { return (long)((tt + bt - 1) / bt) * ((tn + bn - 1) / bn); };
+    const long n1 = blocks(8, 8), n2 = blocks(8, 16), n4 = blocks(16, 16);
+    const double c1 = n1 <= 256 ? 1.2 : std::max(2.0, n1 / 256.0);
+    const double c2 = 1.8 * ((n2 + 255) / 256), c4 = 3.0 * ((n4 + 255) / 256);
+    if (a.ksplit > 1) {
+        if (c2 < c1) return gemm_rows_launch<WT, 4, 4, 2, 4, EPI, AT, KM, true>(a, s);
+        return gemm_rows_launch<WT, 2, 4, 4, 2, EPI, AT, KM, true>(a, s);
+    }
+    if (c4 < c1 && c4 < c2) return gemm_rows_launch<WT, 8, 4, 2, 4, EPI, AT, KM, false>(a, s);
+    if (c2 < c1) return gemm_rows_launch<WT, 4, 4, 2, 4, EPI, AT, KM, false>(a, s);
+    return gemm_rows_launch<WT, 2, 4, 4, 2, EPI, AT, KM, false>(a, s);
+}
+
+// Residual projections of few rows (up to 128 blocks of 128 x 128: 512 rows of
+// the 7B shapes) leave most of the chip idle and hand each K range to a
+// workgroup of its own.
+bool gemm_rows_split(int wtype, int N, int Kp, int T) {
+    return T <= PF_SPLIT_ROWS && gemm_parts_count(wtype, N, Kp, 1) > 1 && (long)((T + 127) / 128) * ((N + 127) / 128) <= 128;
 }
 
 template <int WT, typename AT>
 static hipError_t gemm_rows_epi(int epi, const GemmArgs& a, hipStream_t s) {
     switch (epi) {
+    case EPI_STORE:  // split partial sums
+        if (a.kmaj || a.ksplit < 2 || a.part_stride < (size_t)a.T * a.ldo) return hipErrorInvalidValue;
+        return gemm_rows_launch<WT, 2, 4, 4, 2, EPI_STORE, AT, false, false, true>(a, s);
     case EPI_RESID: return gemm_rows_go<WT, EPI_RESID, AT, false>(a, s);
     case EPI_SWIGLU: return gemm_rows_go<WT, EPI_SWIGLU, AT, true>(a, s);
     case EPI_QKV: return gemm_rows_go<WT, EPI_QKV, AT, false>(a, s);
@@ -178,6 +253,13 @@ hipError_t launch_gemm_rows(int wtype, int epi, const GemmArgs& a, hipStream_t s
 }
 
 // ---------------------------------------------------------------- attention
+
+// The same through the builtin, for stages the compiler can tell apart
+// (separate arrays): it waits for the loads itself.
+__device__ __forceinline__ void lds_load16_b(const void* src, void* dst) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                     (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
 
 // Causal attention of a prefill.  Workgroup = (kv head, QW query tiles of 16
 // rows; the G heads of a group at the same rows follow each other, so its
@@ -221,7 +303,7 @@ __global__ void __launch_bounds__(64 * QW, 2) k_attn_causal(const AttnArgs a, fl
 #pragma unroll
         for (int i = 0; i < LP; ++i) {
             const int f = wave * LP + i, tile = min(split * NTS + f / KF, n_tiles - 1);
-            lds_load16(base + (size_t)tile * TE + (f % KF) * 512, dst + f * 64);
+            lds_load16_b(base + (size_t)tile * TE + (f % KF) * 512, dst + f * 64);
         }
         __builtin_amdgcn_sched_barrier(0);
     };

@@ -500,8 +500,13 @@ hipError_t enqueue_prefill(cas_ctx* c, int T, int logit_rows) {
     RUN(CAS_K_EMBED, launch_embed_chain(et, c->embed, d, f.vocab, c->d_ptok, c->d_sp, T, c->d_h, c->d_row_pos,
                                         c->d_row_slot, c->d_chk, s));
     const size_t kv_layer = (size_t)Hkv * c->ctx_cap * hd * c->es;
-    auto norm = [&](const float* gain) -> hipError_t {
-        return launch_rmsnorm(et, c->d_h, gain, T, d, f.rms_eps, c->d_xn, nullptr, nullptr, nullptr, 0, 0, 127, s);
+    int pend = 0;  // K ranges whose sums the next norm adds to the residual stream
+    const size_t pstride = (size_t)T * d;
+    auto norm = [&](const float* gain, int row0, int rows) -> hipError_t {
+        const hipError_t r = launch_rmsnorm(et, c->d_h + (size_t)row0 * d, gain, rows, d, f.rms_eps, c->d_xn, nullptr,
+                                            nullptr, c->d_gpart + (size_t)row0 * d, pend, pstride, 127, s);
+        pend = 0;
+        return r;
     };
     auto gemm = [&](int epi, int which, const void* W, const void* X, int N, int Kp, GemmArgs g) -> hipError_t {
         g.W = W;
@@ -512,6 +517,12 @@ hipError_t enqueue_prefill(cas_ctx* c, int T, int logit_rows) {
         g.chk = c->d_chk;
         g.kmaj = kProjKMajor[which];
         g.ksplit = gemm_sum_ranges(et, N, Kp, epi == EPI_RESID);
+        if (epi == EPI_RESID && gemm_rows_split(et, N, Kp, T)) {
+            epi = EPI_STORE;
+            g.out = c->d_gpart;
+            g.part_stride = pstride;
+            pend = g.ksplit;
+        }
         return launch_gemm_rows(et, epi, g, s);
     };
     for (int l = 0; l < f.n_layers; ++l) {
@@ -546,17 +557,16 @@ hipError_t enqueue_prefill(cas_ctx* c, int T, int logit_rows) {
         gu.out = c->d_sw;
         gu.ldo = ffn;
         gu.out_k = ffn;
-        RUN(CAS_K_RMSNORM, norm(w.attn_norm));
+        RUN(CAS_K_RMSNORM, norm(w.attn_norm, 0, T));
         RUN(CAS_K_GEMM_QKV, gemm(EPI_QKV, 0, w.wqkv, c->d_xn, c->qkv_rows, c->kp_d, qkv));
         RUN(CAS_K_ATTN, launch_attention_causal(et, at, s));
         RUN(CAS_K_GEMM_O, gemm(EPI_RESID, 1, w.wo, c->d_ao, d, c->kp_q, resid));
-        RUN(CAS_K_RMSNORM, norm(w.ffn_norm));
+        RUN(CAS_K_RMSNORM, norm(w.ffn_norm, 0, T));
         RUN(CAS_K_GEMM_GATEUP, gemm(EPI_SWIGLU, 2, w.wgu, c->d_xn, 2 * ffn, c->kp_d, gu));
         RUN(CAS_K_GEMM_DOWN, gemm(EPI_RESID, 3, w.wd, c->d_sw, d, c->kp_f, resid));
     }
     if (logit_rows > 0) {
-        RUN(CAS_K_RMSNORM, launch_rmsnorm(et, c->d_h + (size_t)(T - logit_rows) * d, c->final_norm, logit_rows, d,
-                                          f.rms_eps, c->d_xn, nullptr, nullptr, nullptr, 0, 0, 127, s));
+        RUN(CAS_K_RMSNORM, norm(c->final_norm, T - logit_rows, logit_rows));
         GemmArgs gh{};
         gh.T = logit_rows;
         gh.N = f.vocab;
@@ -922,7 +932,7 @@ cas_status cas_create(const cas_config* cfg, int device, void* stream, cas_ctx**
     ALLOC(c->d_logits, T * (size_t)f.vocab * 4);
     c->part_bytes = attention_work_bytes(c->ctx_cap, (int)T, f.n_heads, f.head_dim);
     ALLOC(c->d_part, c->part_bytes);
-    ALLOC(c->d_gpart, sizeof(float) * 8 * (size_t)f.max_tree * f.d_model);
+    ALLOC(c->d_gpart, sizeof(float) * 8 * std::max((size_t)f.max_tree, std::min(P, (size_t)PF_SPLIT_ROWS)) * f.d_model);
     ALLOC(c->d_gbuf, T * 8 * 3 * 4);  // per row: 8 argmax parts of (index, value, NaN flag)
     ALLOC(c->d_result, (T + 4) * 4);
     ALLOC(c->d_topk, T * (16 + 16 + 1) * 4);
