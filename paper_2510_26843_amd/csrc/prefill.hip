@@ -27,6 +27,125 @@ __device__ __forceinline__ void stage_wait() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
+// 4 x 4 transpose over the lane groups g = lane / 16: lane group g's v[j]
+// becomes v[g] of lane group j.
+__device__ __forceinline__ void lane_transpose4(uint32_t (&v)[4]) {
+    const auto a = __builtin_amdgcn_permlane32_swap(v[0], v[2], false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(v[1], v[3], false, false);
+    const auto lo = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+    v[0] = lo[0];
+    v[1] = lo[1];
+    v[2] = hi[0];
+    v[3] = hi[1];
+}
+__device__ __forceinline__ uint32_t pack_bf(float x, float y) { return (uint32_t)f2bf(x) | ((uint32_t)f2bf(y) << 16); }
+
+// The bf16 SwiGLU and QKV epilogues of one weight tile over four row tiles
+// (gemm_epilogue's arithmetic) with 16-byte stores: its lanes hold 2- and
+// 4-byte pieces of a row that are 8 consecutive elements of the output, so
+// the four lane groups exchange them, each ending with one row tile's 16
+// bytes; V tiles, whose output runs along the slots, turn through LDS.  The
+// piecewise stores cost the 7B QKV 131 us and gate/up 199 us at
+// 1024 rows, these 115 and 189 (3001 tokens of the 8B shape: 115 -> 99, 317 -> 289).
+constexpr int EP_LDS = 16 * 72;  // 2-byte elements of a wave's V tile: 16 d, 64 slots, padded
+struct RowsPre {
+    int pos[4], slot, vslot;  // RoPE positions of rows 16j + r; slot of row 16g + r, of row 8 (lane % 8)
+    __device__ __forceinline__ void load(const GemmArgs& a, int row0, int lane) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            pos[j] = a.row_pos[min(row0 + 16 * j + (lane & 15), a.T - 1)];
+            if (!dcheck(a.chk, pos[j] >= 0 && pos[j] < a.ctx_cap, CHK_POSITION)) pos[j] = 0;
+        }
+        slot = a.row_slot[min(row0 + lane, a.T - 1)];  // 16 g + r = lane
+        vslot = a.row_slot[min(row0 + 8 * (lane & 7), a.T - 1)];
+    }
+};
+struct RopePre {
+    float2 cs[4], sn[4];  // the lane's two rotation pairs at rows 16j + r
+    __device__ __forceinline__ void load(const GemmArgs& a, int tile, int lane, const RowsPre& rp) {
+        const int hd = a.hd, nb = tile * 16 + 4 * (lane >> 4), p0 = nb % hd / 2, half = hd / 2;
+        const bool rot = tile * 16 < (a.H + a.Hkv) * hd;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const size_t i = rot ? (size_t)rp.pos[j] * half + p0 : 0;
+            cs[j] = *(const float2*)(a.rope_cos + i);
+            sn[j] = *(const float2*)(a.rope_sin + i);
+        }
+    }
+};
+template <int EPI>
+__device__ __forceinline__ void rows_epilogue(const GemmArgs& a, const f32x4 (&v)[4], int tile, int last_tile, int lane,
+                                              int row0, const RowsPre& rp, const RopePre& ro, uint16_t* ep) {
+    static_assert(EPI == EPI_SWIGLU || EPI == EPI_QKV, "bf16 outputs");
+    const int T = a.T, t = row0 + lane;  // row of the lane's stores
+    if constexpr (EPI == EPI_SWIGLU) {
+        uint32_t w[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            w[j] = pack_bf(v[j][0] / (1.0f + expf(-v[j][0])) * v[j][1], v[j][2] / (1.0f + expf(-v[j][2])) * v[j][3]);
+        lane_transpose4(w);
+        const int nto = col_tiles(T);
+        if (t < T) *(uint4*)((uint16_t*)a.out + xt_off(t, tile * 8, nto, 8)) = make_uint4(w[0], w[1], w[2], w[3]);
+        if (tile == last_tile) {  // and the pad columns
+            const int pad = (a.out_k + 127) / 128 * 128 - a.out_k, rows = min(T - row0, 64);
+            for (int i = lane; i < rows * pad; i += 64)
+                ((uint16_t*)a.out)[xt_off(row0 + i / pad, a.out_k + i % pad, nto, 8)] = 0;
+        }
+    } else {
+        const int hd = a.hd, half = hd / 2, qrows = a.H * hd, krows = a.Hkv * hd, n0 = tile * 16;
+        if (n0 < qrows + krows) {
+            uint32_t lo[4], hi[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float a0 = v[j][0], a1 = v[j][1], b0 = v[j][2], b1 = v[j][3];
+                lo[j] = pack_bf(a0 * ro.cs[j].x - a1 * ro.sn[j].x, b0 * ro.cs[j].y - b1 * ro.sn[j].y);
+                hi[j] = pack_bf(a0 * ro.sn[j].x + a1 * ro.cs[j].x, b0 * ro.sn[j].y + b1 * ro.cs[j].y);
+            }
+            lane_transpose4(lo);
+            lane_transpose4(hi);
+            const bool isq = n0 < qrows;
+            const int rel = n0 - (isq ? 0 : qrows), head = rel / hd, d0 = rel % hd / 2;
+            uint16_t *pl, *ph;
+            bool ok = t < T;
+            if (isq) {
+                pl = (uint16_t*)a.out + ((size_t)t * a.H + head) * hd + d0;
+                ph = pl + half;
+            } else {
+                ok = ok && dcheck(a.chk, rp.slot >= 0 && rp.slot < a.ctx_cap, CHK_KV_WRITE);
+                uint16_t* o = (uint16_t*)a.kc + (size_t)head * a.ctx_cap * hd;
+                pl = o + kv_k_tiled(rp.slot, d0, hd);
+                ph = o + kv_k_tiled(rp.slot, d0 + half, hd);
+            }
+            if (ok) {
+                *(uint4*)pl = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+                *(uint4*)ph = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+            }
+        } else {
+            const int rel = n0 - qrows - krows, head = rel / hd, d0 = rel % hd;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) ep[(4 * (lane >> 4) + i) * 72 + 16 * j + (lane & 15)] = f2bf(v[j][i]);
+            asm volatile("" ::: "memory");  // (one wave's LDS operations stay in order)
+            // eight rows of one d per lane: consecutive slots, one 16-byte
+            // piece of the cache where the first is a multiple of 8
+            const int tg = 8 * (lane & 7), n = min(8, T - row0 - tg);
+            uint16_t* o = (uint16_t*)a.vt + (size_t)head * a.ctx_cap * hd;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int d = (lane >> 3) + 8 * h;
+                const uint16_t* e = ep + d * 72 + tg;
+                if (n < 1 || !dcheck(a.chk, rp.vslot >= 0 && rp.vslot + n <= a.ctx_cap, CHK_KV_WRITE)) continue;
+                if (n == 8 && (rp.vslot & 7) == 0) *(i32x4*)(o + kv_v_tiled(rp.vslot, d0 + d, hd)) = *(const i32x4*)e;
+                else
+                    for (int k = 0; k < n; ++k) o[kv_v_tiled(rp.vslot + k, d0 + d, hd)] = e[k];
+            }
+            asm volatile("" ::: "memory");
+        }
+    }
+}
+
 // Prefill: the same linear layers over hundreds to thousands of rows, where
 // the weights are reused and the matrix cores are what counts.  A workgroup
 // computes (16 NW WN) weight rows x (16 TW WT_) activation rows; its WN x WT_
@@ -53,6 +172,8 @@ __global__ void __launch_bounds__(64 * WN * WT_, 2) k_gemm_rows(GemmArgs a) {
     constexpr int SB = (BN + BT) * 1024;                   // bytes of a stage
     static_assert(!is_int<WT>() && !(RNG && SPL), "fp32 and bf16 weights; one way with the ranges");
     static_assert(LA * W == BN && LB * W == BT && D % FRAG_U == 0, "stage shape");
+    constexpr bool BFX = sizeof(AT) == 2 && (EPI == EPI_SWIGLU || EPI == EPI_QKV);  // the 16-byte epilogues
+    static_assert(!BFX || (TW == 4 && 2 * W * EP_LDS <= D * SB), "epilogue shape");
     __shared__ __attribute__((aligned(16))) char sm[D * SB];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -100,6 +221,8 @@ __global__ void __launch_bounds__(64 * WN * WT_, 2) k_gemm_rows(GemmArgs a) {
             pb[i] += more ? bst : 0;
         }
     };
+    RowsPre rp;
+    if constexpr (BFX && EPI == EPI_QKV) rp.load(a, (tt0 + wt * TW) * 16, lane);
     ACC acc[NW][TW], tot[RNG ? NW : 1][RNG ? TW : 1];
 #pragma unroll
     for (int i = 0; i < NW; ++i)
@@ -168,14 +291,28 @@ __global__ void __launch_bounds__(64 * WN * WT_, 2) k_gemm_rows(GemmArgs a) {
     }
     stage_wait<0>();
     mfma_result_pad();
+    const int row0 = (tt0 + wt * TW) * 16, tile0 = tn0 + wn * NW;
+    if (row0 >= a.T) return;
+    if constexpr (BFX) {
+        RopePre ro[2];
+        if constexpr (EPI == EPI_QKV) ro[0].load(a, min(tile0, ntiles - 1), lane, rp);
+        uint16_t* ep = (uint16_t*)sm + wave * EP_LDS;  // every wave is done with the ring
 #pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        const int tile = tn0 + wn * NW + i, row0 = (tt0 + wt * TW) * 16;
-        if (tile >= ntiles || row0 >= a.T) continue;
-        QkvPre<TW> qp;
-        if constexpr (EPI == EPI_QKV) qp.load(a, tile, lane, row0);
-        if constexpr (RNG) gemm_epilogue<WT, TW, EPI, AT>(a, tot[i], tile, ntiles - 1, lane, qp, row0);
-        else gemm_epilogue<WT, TW, EPI, AT>(a, acc[i], tile, ntiles - 1, lane, qp, row0);
+        for (int i = 0; i < NW; ++i) {
+            if (EPI == EPI_QKV && i + 1 < NW) ro[(i + 1) & 1].load(a, min(tile0 + i + 1, ntiles - 1), lane, rp);
+            if (tile0 + i >= ntiles) continue;
+            if constexpr (RNG) rows_epilogue<EPI>(a, tot[i], tile0 + i, ntiles - 1, lane, row0, rp, ro[i & 1], ep);
+            else rows_epilogue<EPI>(a, acc[i], tile0 + i, ntiles - 1, lane, row0, rp, ro[i & 1], ep);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            if (tile0 + i >= ntiles) continue;
+            QkvPre<TW> qp;
+            if constexpr (EPI == EPI_QKV) qp.load(a, tile0 + i, lane, row0);
+            if constexpr (RNG) gemm_epilogue<WT, TW, EPI, AT>(a, tot[i], tile0 + i, ntiles - 1, lane, qp, row0);
+            else gemm_epilogue<WT, TW, EPI, AT>(a, acc[i], tile0 + i, ntiles - 1, lane, qp, row0);
+        }
     }
 }
 
