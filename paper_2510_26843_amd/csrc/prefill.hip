@@ -398,22 +398,27 @@ __device__ __forceinline__ void lds_load16_b(const void* src, void* dst) {
                                      (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
 }
 
-// Causal attention of a prefill.  Workgroup = (kv head, QW query tiles of 16
+// Causal attention of a prefill.  Workgroup = (kv head, four query tiles of 16
 // rows; the G heads of a group at the same rows follow each other, so its
 // waves need about the same slots).  It walks the splits of 256 slots that
-// its rows see; a split's K and then its V pass once through LDS (64 KB each
-// at head_dim 128, direct-to-LDS loads: V arrives under the scores, the next
-// K under the softmax and P V), and each wave computes the split's partial of
+// its rows see; a split's K and then its V pass through LDS in halves (32 KB
+// each at head_dim 128, two buffers, direct-to-LDS loads: each half arrives
+// while the previous one is used), and each wave computes the split's partial of
 // its rows exactly as k_attn_rows does and merges it into its running state
 // exactly as k_attn_merge does, in split order: the same bits as a forward of
 // up to 128 rows, without the partials' trip through memory.  Parts wholly
 // past a tile's last row would add zero and are left out.
-template <int HD, int QW>
-__global__ void __launch_bounds__(64 * QW, 2) k_attn_causal(const AttnArgs a, float scale_log2) {
-    constexpr int UD = HD / 32, DG = HD / 4, NDT = HD / 16, TE = 32 * HD;
-    constexpr int NP = ATT_WAVES, NTS = NP * ATT_TPW, KF = 2 * UD, LP = NTS * KF / QW;
-    static_assert(KF == NDT && LP * QW == NTS * KF, "K and V stages must match");
-    __shared__ i32x4 ks[NTS * KF * 64], vs[NTS * NDT * 64];
+// The VALU work of the softmax bounds it (some 1200 instructions against 192
+// MFMAs per wave and split).  Two workgroups of 64 rows per CU even out the
+// rows' unequal walks: eight waves on 128 KB of whole K and V stages, one
+// workgroup per CU, took 38 us per layer for 1024 tokens of the 7B shape and
+// 93 for 1501 of 8B (after 1500); these take 32 and 86.
+template <int HD>
+__global__ void __launch_bounds__(256, 2) k_attn_causal(const AttnArgs a, float scale_log2) {
+    constexpr int UD = HD / 32, DG = HD / 4, NDT = HD / 16, TE = 32 * HD, QW = 4;
+    constexpr int NP = ATT_WAVES, NTS = NP * ATT_TPW, NTH = NTS / 2, KF = 2 * UD, LP = NTH * KF / QW;
+    static_assert(KF == NDT && LP * QW == NTH * KF, "K and V stages must match");
+    __shared__ i32x4 sa[NTH * KF * 64], sb[NTH * KF * 64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, g = lane >> 4;
@@ -436,10 +441,10 @@ __global__ void __launch_bounds__(64 * QW, 2) k_attn_causal(const AttnArgs a, fl
     }
     const uint16_t* kbase = (const uint16_t*)a.kc + (size_t)kvh * a.ctx_cap * HD + lane * 8;
     const uint16_t* vbase = (const uint16_t*)a.vt + (size_t)kvh * a.ctx_cap * HD + lane * 8;
-    auto load = [&](const uint16_t* base, i32x4* dst, int split) {
+    auto load = [&](const uint16_t* base, i32x4* dst, int split, int half) {
 #pragma unroll
         for (int i = 0; i < LP; ++i) {
-            const int f = wave * LP + i, tile = min(split * NTS + f / KF, n_tiles - 1);
+            const int f = wave * LP + i, tile = min(split * NTS + half * NTH + f / KF, n_tiles - 1);
             lds_load16_b(base + (size_t)tile * TE + (f % KF) * 512, dst + f * 64);
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -448,14 +453,12 @@ __global__ void __launch_bounds__(64 * QW, 2) k_attn_causal(const AttnArgs a, fl
     float L = 0.f, M = -1e30f;
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    load(kbase, ks, 0);
-    __syncthreads();
-    for (int split = 0; split < nsplit; ++split) {
-        const int base = split * ATT_SPLIT;
-        load(vbase, vs, split);
-        float x[NP][ATT_TPW][8], m[NP], Ms = -1e30f;
+    float x[NP][ATT_TPW][8], m[NP], Ms, l;
+    f32x4 o[NDT];
+    auto scores = [&](const i32x4* ks, int base, int half) {
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {
+        for (int ph = 0; ph < NP / 2; ++ph) {
+            const int p = half * (NP / 2) + ph;
             m[p] = -1e30f;
             if (base + p * 32 * ATT_TPW < wslots) {
 #pragma unroll
@@ -466,7 +469,7 @@ __global__ void __launch_bounds__(64 * QW, 2) k_attn_causal(const AttnArgs a, fl
                         S[h2] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                         for (int u = 0; u < UD; ++u)
-                            S[h2] = mfma_step<ET_BF16>(ks[((p * ATT_TPW + tt) * KF + h2 * UD + u) * 64 + lane], Qf[u], S[h2]);
+                            S[h2] = mfma_step<ET_BF16>(ks[((ph * ATT_TPW + tt) * KF + h2 * UD + u) * 64 + lane], Qf[u], S[h2]);
                     }
                     attn_tile_scores(S, bits8(0, vl - (base + (p * ATT_TPW + tt) * 32 + 8 * g)), scale_log2, x[p][tt]);
                 }
@@ -474,35 +477,50 @@ __global__ void __launch_bounds__(64 * QW, 2) k_attn_causal(const AttnArgs a, fl
                 Ms = fmaxf(Ms, m[p]);
             }
         }
-        __syncthreads();  // V is there, K is read
-        if (split + 1 < nsplit) load(kbase, ks, split + 1);
-        if (base < wslots) {
-            f32x4 o[NDT];
-            float l = 0.f;
+    };
+    auto values = [&](const i32x4* vs, int base, int half) {
 #pragma unroll
-            for (int dt = 0; dt < NDT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int ph = 0; ph < NP / 2; ++ph) {
+            const int p = half * (NP / 2) + ph;
+            if (base + p * 32 * ATT_TPW >= wslots) continue;
+            i32x4 Pf[ATT_TPW], Pl[ATT_TPW];
+            const float lp = attn_part_probs<ATT_TPW>(x[p], m[p], Pf, Pl);
+            const float f = attn_merge_weight(m[p], Ms);
 #pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                if (base + p * 32 * ATT_TPW >= wslots) continue;
-                i32x4 Pf[ATT_TPW], Pl[ATT_TPW];
-                const float lp = attn_part_probs<ATT_TPW>(x[p], m[p], Pf, Pl);
-                const float f = attn_merge_weight(m[p], Ms);
+            for (int dt = 0; dt < NDT; ++dt) {
+                f32x4 po = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int dt = 0; dt < NDT; ++dt) {
-                    f32x4 po = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int tt = 0; tt < ATT_TPW; ++tt) {
-                        const i32x4 v = vs[((p * ATT_TPW + tt) * NDT + dt) * 64 + lane];
-                        po = mfma_step<ET_BF16>(v, Pf[tt], po);
-                        po = mfma_step<ET_BF16>(v, Pl[tt], po);
-                    }
-                    attn_merge_o(o[dt], po, f);
+                for (int tt = 0; tt < ATT_TPW; ++tt) {
+                    const i32x4 v = vs[((ph * ATT_TPW + tt) * NDT + dt) * 64 + lane];
+                    po = mfma_step<ET_BF16>(v, Pf[tt], po);
+                    po = mfma_step<ET_BF16>(v, Pl[tt], po);
                 }
-                attn_merge_l(l, lp, f);
+                attn_merge_o(o[dt], po, f);
             }
-            attn_merge_split<NDT>(acc, L, M, o, l, Ms);
+            attn_merge_l(l, lp, f);
         }
-        __syncthreads();  // the next K is there, V is read
+    };
+    load(kbase, sa, 0, 0);
+    __syncthreads();
+    for (int split = 0; split < nsplit; ++split) {
+        const int base = split * ATT_SPLIT;
+        Ms = -1e30f;
+        l = 0.f;
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        load(kbase, sb, split, 1);
+        scores(sa, base, 0);
+        __syncthreads();  // what was loaded is there, what was used is free
+        load(vbase, sa, split, 0);
+        scores(sb, base, 1);
+        __syncthreads();
+        load(vbase, sb, split, 1);
+        values(sa, base, 0);
+        __syncthreads();
+        if (split + 1 < nsplit) load(kbase, sa, split + 1, 0);
+        values(sb, base, 1);
+        if (base < wslots) attn_merge_split<NDT>(acc, L, M, o, l, Ms);
+        __syncthreads();
     }
     const int t = t0 + r;
     if (t < T) {
@@ -520,11 +538,10 @@ hipError_t launch_attention_causal(int atype, const AttnArgs& a, hipStream_t s) 
         return hipErrorInvalidValue;
     if (atype == ET_F32) return launch_attention_f32(a, 1, s);
     if (a.ctx_cap % 32) return hipErrorInvalidValue;
-    constexpr int QW = 8;
-    const int nct = (a.T + 15) / 16 * (a.H / a.Hkv), nblk = (nct + QW - 1) / QW;
+    const int nct = (a.T + 15) / 16 * (a.H / a.Hkv), nblk = (nct + 3) / 4;
     const float scale_log2 = (1.0f / sqrtf((float)a.hd)) * 1.4426950408889634f;
-    if (a.hd == 128) hipLaunchKernelGGL((k_attn_causal<128, QW>), dim3(nblk * a.Hkv), dim3(64 * QW), 0, s, a, scale_log2);
-    else hipLaunchKernelGGL((k_attn_causal<64, QW>), dim3(nblk * a.Hkv), dim3(64 * QW), 0, s, a, scale_log2);
+    if (a.hd == 128) hipLaunchKernelGGL(k_attn_causal<128>, dim3(nblk * a.Hkv), dim3(256), 0, s, a, scale_log2);
+    else hipLaunchKernelGGL(k_attn_causal<64>, dim3(nblk * a.Hkv), dim3(256), 0, s, a, scale_log2);
     return hipGetLastError();
 }
 
