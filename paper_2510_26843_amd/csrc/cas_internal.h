@@ -315,11 +315,12 @@ hipError_t launch_embed_chain(int atype, const void* embed, int d, int vocab, co
                               int T, float* h, int* row_pos, int* row_slot, int* chk, hipStream_t s);
 // Greedy acceptance: per-row argmax of logits [T][V], then the tree walk.
 // result: [0] = n_accepted, [1] = bonus token, [2] = NaN flag, [3..] = node ids.
+// The results of both may lie in pinned host memory.
 hipError_t launch_accept(const float* logits, int T, int V, const int* round_tokens, const int* round_parent,
                          int* argmax_buf, int* result, int* chk, hipStream_t s);
 // Top-K ids (value descending, lower id on ties; -1 past the finite
 // entries) and softmax probabilities of each of n logits rows [n][V]; K in
-// [1, 16]; flag[row] set to 1 when the row holds a NaN (not cleared here).
+// [1, 16]; flag[row]: 1 when the row holds a NaN, else 0.
 hipError_t launch_topk(const float* logits, int n, int V, int K, int* ids, float* probs, int* flag, hipStream_t s);
 // Move accepted slots Lc+acc[j] -> Lc+j in every layer (K and V caches).
 hipError_t launch_compact(int atype, void* kc, void* vt, int L, int Hkv, int hd, int ctx_cap,

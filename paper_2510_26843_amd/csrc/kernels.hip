@@ -2018,22 +2018,33 @@ __global__ void __launch_bounds__(TOPK_THREADS) k_topk(const float* logits, int 
     for (int k = 0; k < KL; ++k) { lv[k] = -INFINITY; li[k] = 0x7fffffff; }
     float m = -INFINITY, s = 0.f;
     int nan = 0;
-    for (int v = tid; v < V; v += TOPK_THREADS) {
-        const float y = x[v];
-        if (y != y) { nan = 1; continue; }
-        if (y > m) { s = (m == -INFINITY ? 0.f : s * __expf(m - y)) + 1.f; m = y; }
-        else s += __expf(y - m);
-        if (tk_better(y, v, lv[KL - 1], li[KL - 1])) {
-            // insert into the sorted list: shift the worse entries down
-            float cv = y;
-            int ci = v;
+    // TK_BATCH loads in flight per thread, taken in index order: with one at a
+    // time the scan waited for memory at each (the figures are at cas_topk)
+    constexpr int TK_BATCH = 8;
+    for (int v0 = tid; v0 < V; v0 += TK_BATCH * TOPK_THREADS) {
+        float yb[TK_BATCH];
 #pragma unroll
-            for (int k = 0; k < KL; ++k) {
-                if (tk_better(cv, ci, lv[k], li[k])) {
-                    const float tv = lv[k];
-                    const int ti = li[k];
-                    lv[k] = cv; li[k] = ci;
-                    cv = tv; ci = ti;
+        for (int b = 0; b < TK_BATCH; ++b) yb[b] = x[min(v0 + b * TOPK_THREADS, V - 1)];
+#pragma unroll
+        for (int b = 0; b < TK_BATCH; ++b) {
+            const int v = v0 + b * TOPK_THREADS;
+            if (v >= V) break;
+            const float y = yb[b];
+            if (y != y) { nan = 1; continue; }
+            if (y > m) { s = (m == -INFINITY ? 0.f : s * __expf(m - y)) + 1.f; m = y; }
+            else s += __expf(y - m);
+            if (tk_better(y, v, lv[KL - 1], li[KL - 1])) {
+                // insert into the sorted list: shift the worse entries down
+                float cv = y;
+                int ci = v;
+#pragma unroll
+                for (int k = 0; k < KL; ++k) {
+                    if (tk_better(cv, ci, lv[k], li[k])) {
+                        const float tv = lv[k];
+                        const int ti = li[k];
+                        lv[k] = cv; li[k] = ci;
+                        cv = tv; ci = ti;
+                    }
                 }
             }
         }
@@ -2083,7 +2094,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) k_topk(const float* logits, int 
             li[KL - 1] = 0x7fffffff;
         }
     }
-    if (tid == 0 && nan) flag[row] = 1;
+    if (tid == 0) flag[row] = nan ? 1 : 0;
 }
 
 hipError_t launch_topk(const float* logits, int n, int V, int K, int* ids, float* probs, int* flag, hipStream_t s) {
@@ -2112,10 +2123,18 @@ __global__ void __launch_bounds__(256) k_accept_argmax(const float* logits, int 
     const float* row = logits + (size_t)t * V;
     float best = -INFINITY;
     int bi = 0x7fffffff, nan = 0;
-    for (int v = lo + threadIdx.x; v < hi; v += 256) {
-        const float x = row[v];
-        if (x != x) nan = 1;
-        else if (bi == 0x7fffffff || x > best) { best = x; bi = v; }
+    constexpr int NB = 8;  // loads in flight per thread, taken in index order
+    for (int v0 = lo + threadIdx.x; v0 < hi; v0 += NB * 256) {
+        float x[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) x[b] = row[min(v0 + b * 256, hi - 1)];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int v = v0 + b * 256;
+            if (v >= hi) break;
+            if (x[b] != x[b]) nan = 1;
+            else if (bi == 0x7fffffff || x[b] > best) { best = x[b]; bi = v; }
+        }
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {

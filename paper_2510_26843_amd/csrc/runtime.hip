@@ -8,6 +8,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -36,6 +37,7 @@ constexpr int kProjKMajor[4] = {0, 0, 1, 0};
 constexpr int kPrefillRows = 2048;
 // Longer prompts run as prefill blocks, shorter ones as tree chunks.
 constexpr int kPrefillTree = 128;
+constexpr int kRoundNodes = 128;  // nodes a round can have
 constexpr size_t kStageBytes = 16 + 4 * (size_t)kPrefillRows;
 
 struct LayerW {
@@ -116,11 +118,9 @@ struct cas_ctx {
     float* d_gpart = nullptr;  // split-K partial sums of the O / down projections [8][max_tree][d_model]
     size_t part_bytes = 0;
     int* d_gbuf = nullptr;
-    int* d_result = nullptr;
     int* d_acc = nullptr;
     int* h_result = nullptr;  // pinned
-    int* d_topk = nullptr;    // [max_tree][16] ids, [max_tree][16] probabilities, [max_tree] NaN flags
-    int* h_topk = nullptr;    // pinned copy of the same
+    int* h_topk = nullptr;    // pinned: [max_tree][16] ids, [max_tree][16] probabilities, [max_tree] NaN flags
 
     Stage stage[kStages];
     int stage_i = 0;
@@ -640,13 +640,19 @@ cas_status do_forward(cas_ctx* c, const int32_t* tokens, const int32_t* parent, 
     hipEvent_t ev = nullptr;
     unsigned char* buf = next_stage(c, &ev);
     if (!buf) return fail(c, CAS_ERR_DEVICE, "staging buffer wait failed");
+    // (one copy: the step parameters, the round's tokens and its parents lie
+    // together on the device as in the buffer, where there were three copies;
+    // the figures are at cas_topk)
     StepParams sp{c->Lc, node_offset, node_offset + n, c->chk_cap ? c->chk_cap : c->ctx_cap};
+    int32_t* htok = (int32_t*)(buf + 16);
+    int32_t* hpar = htok + kRoundNodes;
     memcpy(buf, &sp, sizeof sp);
-    memcpy(buf + 16, tokens, sizeof(int32_t) * n);
-    memcpy(buf + 16 + 4 * 128, parent, sizeof(int32_t) * n);
-    HIPCHK(c, hipMemcpyAsync(c->d_sp, buf, sizeof sp, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->d_rtok + node_offset, buf + 16, 4 * (size_t)n, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->d_rpar + node_offset, buf + 16 + 4 * 128, 4 * (size_t)n, hipMemcpyHostToDevice,
+    std::copy(c->token.begin(), c->token.begin() + node_offset, htok);
+    std::copy(c->parent.begin(), c->parent.begin() + node_offset, hpar);
+    memcpy(htok + node_offset, tokens, sizeof(int32_t) * n);
+    memset(htok + node_offset + n, 0, sizeof(int32_t) * (kRoundNodes - node_offset - n));
+    memcpy(hpar + node_offset, parent, sizeof(int32_t) * n);
+    HIPCHK(c, hipMemcpyAsync(c->d_sp, buf, 16 + 4 * ((size_t)kRoundNodes + node_offset + n), hipMemcpyHostToDevice,
                              c->stream));
     HIPCHK(c, hipEventRecord(ev, c->stream));
 
@@ -911,9 +917,10 @@ cas_status cas_create(const cas_config* cfg, int device, void* stream, cas_ctx**
     const size_t P = c->pf_rows = std::max(f.max_tree, std::min(f.max_ctx, kPrefillRows));
     const size_t PT = 16 * (size_t)std::max(8, col_tiles(c->pf_rows));
     ALLOC(c->d_ptok, P * 4);
-    ALLOC(c->d_rtok, T * 4);
-    ALLOC(c->d_rpar, T * 4);
-    ALLOC(c->d_sp, sizeof(StepParams));
+    static_assert(sizeof(StepParams) == 16 && kStageBytes >= 16 + 8 * kRoundNodes, "one upload per forward");
+    ALLOC(c->d_sp, 16 + 8 * kRoundNodes);  // step parameters, then the round's tokens and parents
+    c->d_rtok = (int*)(c->d_sp + 1);
+    c->d_rpar = c->d_rtok + kRoundNodes;
     ALLOC(c->d_chk, 16);
     if (hipMemset(c->d_chk, 0, 16) != hipSuccess) return cleanup(CAS_ERR_DEVICE, "hipMemset of the check word");
     ALLOC(c->d_row_pos, P * 4);
@@ -934,10 +941,8 @@ cas_status cas_create(const cas_config* cfg, int device, void* stream, cas_ctx**
     ALLOC(c->d_part, c->part_bytes);
     ALLOC(c->d_gpart, sizeof(float) * 8 * std::max((size_t)f.max_tree, std::min(P, (size_t)PF_SPLIT_ROWS)) * f.d_model);
     ALLOC(c->d_gbuf, T * 8 * 3 * 4);  // per row: 8 argmax parts of (index, value, NaN flag)
-    ALLOC(c->d_result, (T + 4) * 4);
-    ALLOC(c->d_topk, T * (16 + 16 + 1) * 4);
     ALLOC(c->d_acc, (T + 1) * 4);
-    if (hipMemset(c->d_rtok, 0, T * 4) != hipSuccess || hipMemset(c->d_rpar, 0xff, T * 4) != hipSuccess)
+    if (hipMemset(c->d_rtok, 0, kRoundNodes * 4) != hipSuccess || hipMemset(c->d_rpar, 0xff, kRoundNodes * 4) != hipSuccess)
         return cleanup(CAS_ERR_DEVICE, "hipMemset of the round arrays");
     if (hipHostMalloc((void**)&c->h_result, (T + 4) * 4, hipHostMallocDefault) != hipSuccess)
         return cleanup(CAS_ERR_OOM, "hipHostMalloc");
@@ -1182,11 +1187,10 @@ cas_status cas_accept_tree(cas_ctx* c, int32_t greedy, int32_t* accepted, int32_
         return fail(c, CAS_ERR_STATE, "cas_accept_tree needs a verify call covering the whole round");
     const int T = c->n_nodes;
     hipError_t e = timed(c, CAS_K_ACCEPT, [&]() -> hipError_t {
-        return launch_accept(c->d_logits, T, c->cfg.vocab, c->d_rtok, c->d_rpar, c->d_gbuf, c->d_result, c->d_chk,
-                             c->stream);
+        return launch_accept(c->d_logits, T, c->cfg.vocab, c->d_rtok, c->d_rpar, c->d_gbuf, c->h_result, c->d_chk,
+                             c->stream);  // the few words of the result go straight to pinned memory
     });
     if (e != hipSuccess) return hip_fail(c, e, "acceptance launch");
-    HIPCHK(c, hipMemcpyAsync(c->h_result, c->d_result, sizeof(int) * (size_t)(T + 3), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     cas_status cst = poll_checks(c);
     if (cst != CAS_OK) return cst;
@@ -1207,20 +1211,18 @@ cas_status cas_topk(cas_ctx* c, int32_t n, int32_t K, int32_t* ids, float* probs
     if (n != c->logits_rows)
         return fail(c, CAS_ERR_ARG, "n must equal the last forward's row count " + std::to_string(c->logits_rows));
     const int cap = c->cfg.max_tree;
-    int* d_ids = c->d_topk;
-    float* d_p = (float*)(c->d_topk + (size_t)cap * 16);
-    int* d_flag = c->d_topk + (size_t)cap * 32;
-    HIPCHK(c, hipMemsetAsync(d_flag, 0, sizeof(int) * (size_t)n, c->stream));
-    hipError_t e = timed(c, CAS_K_TOPK, [&]() -> hipError_t {
-        return launch_topk(c->d_logits, n, c->cfg.vocab, K, d_ids, d_p, d_flag, c->stream);
-    });
-    if (e != hipSuccess) return hip_fail(c, e, "top-K launch");
+    // the kernel writes its few words per row straight to pinned memory: no
+    // clear before it and no copies behind it.  With the batched loads of the
+    // top-K and argmax scans and one upload per forward: 13B W8A8 draft of
+    // seven rows (2 layers and the head) 329 -> 310 us, round of the fp32
+    // decoder 332 -> 308, of 7B (8 layers) 1334 -> 1320
     int* h_ids = c->h_topk;
     float* h_p = (float*)(c->h_topk + (size_t)cap * 16);
     int* h_flag = c->h_topk + (size_t)cap * 32;
-    HIPCHK(c, hipMemcpyAsync(h_ids, d_ids, sizeof(int) * (size_t)n * K, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(h_p, d_p, sizeof(float) * (size_t)n * K, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(h_flag, d_flag, sizeof(int) * (size_t)n, hipMemcpyDeviceToHost, c->stream));
+    hipError_t e = timed(c, CAS_K_TOPK, [&]() -> hipError_t {
+        return launch_topk(c->d_logits, n, c->cfg.vocab, K, h_ids, h_p, h_flag, c->stream);
+    });
+    if (e != hipSuccess) return hip_fail(c, e, "top-K launch");
     HIPCHK(c, hipStreamSynchronize(c->stream));
     cas_status cst = poll_checks(c);
     if (cst != CAS_OK) return cst;

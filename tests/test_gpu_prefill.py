@@ -19,6 +19,8 @@ SHAPES = {
     "tall": S("tall", 2, 256, 4, 2, 128, 4416, 512, 1e4, 1e-6, "bf16"),
     # tall QKV, rows of more than one block's tiles
     "mha": S("mha", 1, 1024, 24, 24, 128, 4448, 512, 1e4, 1e-6, "bf16"),
+    # rows of more than 4096 elements in the norms
+    "wide": S("wide", 1, 4608, 2, 2, 128, 512, 512, 1e4, 1e-6, "bf16"),
 }
 
 
