@@ -27,13 +27,16 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0  # MI355X HBM3E
-KERNELS_SRC = os.path.join(ROOT, "paper_2510_26843_amd", "csrc", "kernels.hip")
+KERNELS_SRC = [os.path.join(ROOT, "paper_2510_26843_amd", "csrc", f) for f in ("kernels.hip", "kernel_common.h")]
 TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "gemm_gateup_7b_t32_traffic.json")
 
 
 def kernels_sha256():
-    with open(KERNELS_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    h = hashlib.sha256()
+    for path in KERNELS_SRC:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def measured_traffic():

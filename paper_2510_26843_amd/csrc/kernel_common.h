@@ -240,6 +240,12 @@ struct QkvPre {
     }
 };
 
+// The rotation of a pair, with its fused step spelled out: left to the
+// compiler, one instantiation fused the other product and rounded one key
+// element in half a million differently.
+__device__ __forceinline__ float rope_lo(float x0, float x1, float cs, float sn) { return fmaf(x0, cs, -(x1 * sn)); }
+__device__ __forceinline__ float rope_hi(float x0, float x1, float cs, float sn) { return fmaf(x0, sn, x1 * cs); }
+
 // Two consecutive activation values (4-byte aligned for bf16, 8 for fp32).
 __device__ __forceinline__ void st2(uint16_t* p, size_t o, float x, float y) {
     *(uint32_t*)(p + o) = (uint32_t)f2bf(x) | ((uint32_t)f2bf(y) << 16);
@@ -304,8 +310,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, const typename 
                 for (int p = 0; p < 2; ++p) {
                     const float cs = qp.cs[j][p], sn = qp.sn[j][p];
                     const float x0 = v[2 * p], x1 = v[2 * p + 1];
-                    lo[p] = x0 * cs - x1 * sn;
-                    hi[p] = x0 * sn + x1 * cs;
+                    lo[p] = rope_lo(x0, x1, cs, sn);
+                    hi[p] = rope_hi(x0, x1, cs, sn);
                 }
                 // the pairs p0, p0 + 1 (p0 even) are adjacent in q and in both K layouts
                 if (isq) {

@@ -34,7 +34,8 @@ import os
 import re
 import sys
 
-KERNELS_SRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", "kernels.hip")
+KERNELS_SRC = [os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", f)
+               for f in ("kernels.hip", "kernel_common.h")]
 
 
 def short_name(name: str) -> str:
@@ -118,8 +119,11 @@ def traffic(args) -> dict:
     sw = args.copy_bytes / (cw * 1024.0)
     fetch_b = kf * 1024.0 * sf
     write_b = kw * 1024.0 * sw
-    with open(KERNELS_SRC, "rb") as fh:
-        sha = hashlib.sha256(fh.read()).hexdigest()
+    h = hashlib.sha256()
+    for path in KERNELS_SRC:
+        with open(path, "rb") as fh:
+            h.update(fh.read())
+    sha = h.hexdigest()
     return {"kernel": args.kernel, "grid_size": args.grid, "dispatches": [nkf, nkw],
             "fetch_kib_per_dispatch": round(kf, 3), "write_kib_per_dispatch": round(kw, 3),
             "copy_bytes": args.copy_bytes, "copy_fetch_kib": round(cf, 3), "copy_write_kib": round(cw, 3),
