@@ -241,10 +241,16 @@ struct QkvPre {
 };
 
 // The rotation of a pair, with its fused step spelled out: left to the
-// compiler, one instantiation fused the other product and rounded one key
-// element in half a million differently.
+// compiler, each instantiation fuses one product of the sum or the other, and
+// one bf16 key or query element in some 100 000 rounds differently.  The forms
+// are those that the kernels have had from the start, so logits and KV keep
+// their bits: fma(x1, cos, x0 sin) for fp32 accumulators (every tree size and
+// the prefill alike) and for integer ones of two tiles per wave; the integer
+// kernels of one tile per wave (X0) fuse the other product.
 __device__ __forceinline__ float rope_lo(float x0, float x1, float cs, float sn) { return fmaf(x0, cs, -(x1 * sn)); }
-__device__ __forceinline__ float rope_hi(float x0, float x1, float cs, float sn) { return fmaf(x0, sn, x1 * cs); }
+template <bool X0 = false> __device__ __forceinline__ float rope_hi(float x0, float x1, float cs, float sn) {
+    return X0 ? fmaf(x0, sn, x1 * cs) : fmaf(x1, cs, x0 * sn);
+}
 
 // Two consecutive activation values (4-byte aligned for bf16, 8 for fp32).
 __device__ __forceinline__ void st2(uint16_t* p, size_t o, float x, float y) {
@@ -253,8 +259,8 @@ __device__ __forceinline__ void st2(uint16_t* p, size_t o, float x, float y) {
 __device__ __forceinline__ void st2(float* p, size_t o, float x, float y) { *(float2*)(p + o) = make_float2(x, y); }
 
 // Epilogue of one 16-row weight tile: lane holds y[n = 16*tile + 4g + i][t = row0 + 16j + r].
-// qp: the tile's preloaded QKV operands (EPI_QKV only).
-template <int WT, int NT, int EPI, typename AT>
+// qp: the tile's preloaded QKV operands (EPI_QKV only).  TPW: tiles per wave.
+template <int WT, int NT, int EPI, typename AT, int TPW = 1>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, const typename WTr<WT>::acc_t (&acc)[NT], int tile,
                                               int last_tile, int lane, const QkvPre<NT>& qp, int row0 = 0) {
     const int r = lane & 15, g = lane >> 4, T = a.T;
@@ -311,7 +317,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, const typename 
                     const float cs = qp.cs[j][p], sn = qp.sn[j][p];
                     const float x0 = v[2 * p], x1 = v[2 * p + 1];
                     lo[p] = rope_lo(x0, x1, cs, sn);
-                    hi[p] = rope_hi(x0, x1, cs, sn);
+                    hi[p] = rope_hi<is_int<WT>() && TPW == 1>(x0, x1, cs, sn);
                 }
                 // the pairs p0, p0 + 1 (p0 even) are adjacent in q and in both K layouts
                 if (isq) {

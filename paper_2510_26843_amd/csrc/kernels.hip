@@ -437,12 +437,12 @@ __global__ void __launch_bounds__(64 * WAVES) k_gemm_wide(const GemmArgs a) {
     }
     if (gridDim.y == 1) {
 #pragma unroll
-        for (int t = 0; t < TPW; ++t) gemm_epilogue<WT, NT, EPI, AT>(ae, acc[t], tile0 + t, a.N / 16 - 1, lane, qp[t]);
+        for (int t = 0; t < TPW; ++t) gemm_epilogue<WT, NT, EPI, AT, TPW>(ae, acc[t], tile0 + t, a.N / 16 - 1, lane, qp[t]);
     } else {
         GemmArgs b = ae;
         b.out = (float*)a.out + blockIdx.y * a.part_stride;
 #pragma unroll
-        for (int t = 0; t < TPW; ++t) gemm_epilogue<WT, NT, EPI, AT>(b, acc[t], tile0 + t, a.N / 16 - 1, lane, qp[t]);
+        for (int t = 0; t < TPW; ++t) gemm_epilogue<WT, NT, EPI, AT, TPW>(b, acc[t], tile0 + t, a.N / 16 - 1, lane, qp[t]);
     }
 }
 
