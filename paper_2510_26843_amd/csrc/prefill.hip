@@ -401,7 +401,9 @@ hipError_t launch_gemm_rows(int wtype, int epi, const GemmArgs& a, hipStream_t s
 // ---------------------------------------------------------------- attention
 
 // The same through the builtin, for stages the compiler can tell apart
-// (separate arrays): it waits for the loads itself.
+// (separate arrays): it waits for a wave's own loads before that wave's reads.
+// The other waves' reads are what stage_wait<0>() is for: every wave's loads
+// have landed before the barrier lets any of them read.
 __device__ __forceinline__ void lds_load16_b(const void* src, void* dst) {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                      (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
@@ -510,7 +512,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_causal(const AttnArgs a, float 
         }
     };
     load(kbase, sa, 0, 0);
-    __syncthreads();
+    stage_wait<0>();
     for (int split = 0; split < nsplit; ++split) {
         const int base = split * ATT_SPLIT;
         Ms = -1e30f;
@@ -519,17 +521,17 @@ __global__ void __launch_bounds__(256, 2) k_attn_causal(const AttnArgs a, float 
         for (int dt = 0; dt < NDT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
         load(kbase, sb, split, 1);
         scores(sa, base, 0);
-        __syncthreads();  // what was loaded is there, what was used is free
+        stage_wait<0>();  // what was loaded is there, what was used is free
         load(vbase, sa, split, 0);
         scores(sb, base, 1);
-        __syncthreads();
+        stage_wait<0>();
         load(vbase, sb, split, 1);
         values(sa, base, 0);
-        __syncthreads();
+        stage_wait<0>();
         if (split + 1 < nsplit) load(kbase, sa, split + 1, 0);
         values(sb, base, 1);
         if (base < wslots) attn_merge_split<NDT>(acc, L, M, o, l, Ms);
-        __syncthreads();
+        stage_wait<0>();
     }
     const int t = t0 + r;
     if (t < T) {
