@@ -114,8 +114,11 @@ cas_status cas_build_int4(cas_ctx* ctx);
 
 /* Commit n tokens as a causal sequence after the committed prefix (prefill):
  * up to 128 in chunks of at most max_tree, more in blocks of up to 2048 rows.
- * The KV has the same bits either way.  Leaves no round open; the logits are
- * those of the last (n - 1) % max_tree + 1 tokens. */
+ * The first call of the second kind allocates the blocks' buffers (0.2 GB at
+ * the 7B to 13B shapes, freed with the context); where the device has no room
+ * for them, the blocks are smaller or the prompt runs in chunks.  The KV has
+ * the same bits either way.  Leaves no round open; the logits are those of the
+ * last (n - 1) % max_tree + 1 tokens. */
 cas_status cas_prefill(cas_ctx* ctx, const int32_t* tokens, int32_t n);
 
 /* Write committed KV of one layer directly (a cache restored from elsewhere):
@@ -296,10 +299,15 @@ cas_status cas_sync(cas_ctx* ctx);
  *                          inside the real cache.  CAS_ERR_UNSUPPORTED in a
  *                          release build; cap outside [0, max_ctx]:
  *                          CAS_ERR_ARG
+ *   cas_debug_limit_prefill  makes the allocation of a prefill's buffers fail
+ *                          for more than rows rows (-1: no limit), as it does
+ *                          on a full device.  CAS_ERR_UNSUPPORTED in a
+ *                          release build
  */
 int32_t cas_debug_build(void);
 cas_status cas_debug_check(cas_ctx* ctx, int32_t* code);
 cas_status cas_debug_limit_slots(cas_ctx* ctx, int32_t cap);
+cas_status cas_debug_limit_prefill(cas_ctx* ctx, int32_t rows);
 
 #ifdef __cplusplus
 }

@@ -48,7 +48,8 @@ EXPORTS = ("cas_create", "cas_destroy", "cas_last_error", "cas_create_error", "c
            "cas_op_attention_work_bytes", "cas_op_copy", "cas_op_rmsnorm", "cas_op_rmsnorm_work_bytes",
            "cas_op_attn_merge", "cas_op_attn_merge_work_bytes", "cas_op_gemm_qx", "cas_op_gemm_qx_splits",
            "cas_op_gemm_qx_work_bytes", "cas_op_attention_noalloc", "cas_op_attention_noalloc_max_bytes",
-           "cas_debug_build", "cas_debug_check", "cas_debug_limit_slots", "cas_set_gemv")
+           "cas_debug_build", "cas_debug_check", "cas_debug_limit_slots",
+           "cas_debug_limit_prefill", "cas_set_gemv")
 # device check codes (cas_debug_check)
 DEVICE_CHECKS = ["none", "tree size", "token id", "parent order", "slot capacity", "RoPE position",
                  "KV write slot", "attention slots", "compaction path", "acceptance parent"]
@@ -130,6 +131,7 @@ def lib(debug: bool = False):
             "cas_debug_build": ([], I),
             "cas_debug_check": ([P, P], I),
             "cas_debug_limit_slots": ([P, I], I),
+            "cas_debug_limit_prefill": ([P, I], I),
         }
         for name, (args, res) in sig.items():
             fn = getattr(L, name)
@@ -347,6 +349,11 @@ class Model:
         """Make the device checks allow only KV slots < cap (0: the whole
         cache).  Debug build only."""
         self._chk(self._L.cas_debug_limit_slots(self.h, int(cap)))
+
+    def debug_limit_prefill(self, rows: int) -> None:
+        """Make the allocation of a prefill's buffers fail for more than
+        `rows` rows (-1: no limit).  Debug build only."""
+        self._chk(self._L.cas_debug_limit_prefill(self.h, int(rows)))
 
 
 # ----------------------------------------------------------------------------

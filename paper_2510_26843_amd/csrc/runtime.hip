@@ -32,9 +32,11 @@ constexpr size_t kMaxGraphs = 64;   // captured forwards kept at once
 // 482 us per forward), and QKV and down lost 3-4%: they stay tile-major.
 constexpr int kProjKMajor[4] = {0, 0, 1, 0};
 // Rows a prefill runs through the layers at once: enough that the weights are
-// read seldom and the 256-row tiles fill the chip, at 0.3 GB of buffers for
-// the widest model shape.
+// read seldom and the 256-row tiles fill the chip, at 0.2 GB of buffers for
+// the 7B to 13B shapes.  Fewer where the device has no room for that many;
+// below the least, prompts run as tree chunks.
 constexpr int kPrefillRows = 2048;
+constexpr int kPrefillRowsMin = 512;
 // Longer prompts run as prefill blocks, shorter ones as tree chunks.
 constexpr int kPrefillTree = 128;
 constexpr int kRoundNodes = 128;  // nodes a round can have
@@ -58,6 +60,22 @@ struct Stage {
     unsigned char* host = nullptr;
     hipEvent_t ev = nullptr;
     bool pending = false;
+};
+
+// Buffers of the prefill blocks, one allocation: the activations of up to
+// `rows` rows, the tiled ones in whole 256-row tiles, and the split-K sums of
+// blocks of up to PF_SPLIT_ROWS rows.
+struct PrefillBufs {
+    int rows = 0;  // 0: not allocated
+    int* tok = nullptr;
+    int* row_pos = nullptr;
+    int* row_slot = nullptr;
+    float* h = nullptr;
+    void* xn = nullptr;
+    void* q = nullptr;
+    void* ao = nullptr;
+    void* sw = nullptr;
+    float* gpart = nullptr;
 };
 
 struct ProfRec {
@@ -96,8 +114,8 @@ struct cas_ctx {
     int Lc = 0, n_nodes = 0, verified_n = 0, logits_rows = 0;
     std::vector<int> parent, token;
 
-    int pf_rows = 0;        // rows of the activation buffers (a prefill's; at least max_tree)
-    int* d_ptok = nullptr;  // tokens of a prefill's rows
+    PrefillBufs pf;       // taken at the first long prompt
+    int chk_pf = -1;      // most rows they may be allocated for (CAS_DEBUG builds; -1: no limit)
     int* d_rtok = nullptr;
     int* d_rpar = nullptr;
     StepParams* d_sp = nullptr;
@@ -488,6 +506,7 @@ hipError_t enqueue_forward(cas_ctx* c, int T, const uint8_t* skip, int aq) {
 // the final norm and LM head of the last rows, as after such a forward.
 hipError_t enqueue_prefill(cas_ctx* c, int T, int logit_rows) {
     const cas_config& f = c->cfg;
+    const PrefillBufs& m = c->pf;
     const int d = f.d_model, H = f.n_heads, Hkv = f.n_kv_heads, hd = f.head_dim, ffn = f.ffn_dim;
     const int et = c->et;
     hipStream_t s = c->stream;
@@ -497,14 +516,14 @@ hipError_t enqueue_prefill(cas_ctx* c, int T, int logit_rows) {
         e = timed(c, (cls), [&]() -> hipError_t { return call; }); \
         if (e != hipSuccess) return e;                        \
     } while (0)
-    RUN(CAS_K_EMBED, launch_embed_chain(et, c->embed, d, f.vocab, c->d_ptok, c->d_sp, T, c->d_h, c->d_row_pos,
-                                        c->d_row_slot, c->d_chk, s));
+    RUN(CAS_K_EMBED, launch_embed_chain(et, c->embed, d, f.vocab, m.tok, c->d_sp, T, m.h, m.row_pos,
+                                        m.row_slot, c->d_chk, s));
     const size_t kv_layer = (size_t)Hkv * c->ctx_cap * hd * c->es;
     int pend = 0;  // K ranges whose sums the next norm adds to the residual stream
     const size_t pstride = (size_t)T * d;
     auto norm = [&](const float* gain, int row0, int rows) -> hipError_t {
-        const hipError_t r = launch_rmsnorm(et, c->d_h + (size_t)row0 * d, gain, rows, d, f.rms_eps, c->d_xn, nullptr,
-                                            nullptr, c->d_gpart + (size_t)row0 * d, pend, pstride, 127, s);
+        const hipError_t r = launch_rmsnorm(et, m.h + (size_t)row0 * d, gain, rows, d, f.rms_eps, m.xn, nullptr,
+                                            nullptr, m.gpart + (size_t)row0 * d, pend, pstride, 127, s);
         pend = 0;
         return r;
     };
@@ -519,7 +538,7 @@ hipError_t enqueue_prefill(cas_ctx* c, int T, int logit_rows) {
         g.ksplit = gemm_sum_ranges(et, N, Kp, epi == EPI_RESID);
         if (epi == EPI_RESID && gemm_rows_split(et, N, Kp, T)) {
             epi = EPI_STORE;
-            g.out = c->d_gpart;
+            g.out = m.gpart;
             g.part_stride = pstride;
             pend = g.ksplit;
         }
@@ -528,11 +547,11 @@ hipError_t enqueue_prefill(cas_ctx* c, int T, int logit_rows) {
     for (int l = 0; l < f.n_layers; ++l) {
         const LayerW& w = c->layers[l];
         AttnArgs at{};
-        at.q = c->d_q;
+        at.q = m.q;
         at.kc = (char*)c->kc + kv_layer * l;
         at.vt = (char*)c->vt + kv_layer * l;
         at.sp = c->d_sp;
-        at.out = c->d_ao;
+        at.out = m.ao;
         at.out_tiled = 1;
         at.T = T;
         at.H = H;
@@ -541,29 +560,29 @@ hipError_t enqueue_prefill(cas_ctx* c, int T, int logit_rows) {
         at.ctx_cap = c->ctx_cap;
         at.chk = c->d_chk;
         GemmArgs qkv{}, resid{}, gu{};
-        qkv.out = c->d_q;
+        qkv.out = m.q;
         qkv.rope_cos = c->rope_cos;
         qkv.rope_sin = c->rope_sin;
-        qkv.row_pos = c->d_row_pos;
-        qkv.row_slot = c->d_row_slot;
+        qkv.row_pos = m.row_pos;
+        qkv.row_slot = m.row_slot;
         qkv.kc = (void*)at.kc;
         qkv.vt = (void*)at.vt;
         qkv.H = H;
         qkv.Hkv = Hkv;
         qkv.hd = hd;
         qkv.ctx_cap = c->ctx_cap;
-        resid.out = c->d_h;
+        resid.out = m.h;
         resid.ldo = d;
-        gu.out = c->d_sw;
+        gu.out = m.sw;
         gu.ldo = ffn;
         gu.out_k = ffn;
         RUN(CAS_K_RMSNORM, norm(w.attn_norm, 0, T));
-        RUN(CAS_K_GEMM_QKV, gemm(EPI_QKV, 0, w.wqkv, c->d_xn, c->qkv_rows, c->kp_d, qkv));
+        RUN(CAS_K_GEMM_QKV, gemm(EPI_QKV, 0, w.wqkv, m.xn, c->qkv_rows, c->kp_d, qkv));
         RUN(CAS_K_ATTN, launch_attention_causal(et, at, s));
-        RUN(CAS_K_GEMM_O, gemm(EPI_RESID, 1, w.wo, c->d_ao, d, c->kp_q, resid));
+        RUN(CAS_K_GEMM_O, gemm(EPI_RESID, 1, w.wo, m.ao, d, c->kp_q, resid));
         RUN(CAS_K_RMSNORM, norm(w.ffn_norm, 0, T));
-        RUN(CAS_K_GEMM_GATEUP, gemm(EPI_SWIGLU, 2, w.wgu, c->d_xn, 2 * ffn, c->kp_d, gu));
-        RUN(CAS_K_GEMM_DOWN, gemm(EPI_RESID, 3, w.wd, c->d_sw, d, c->kp_f, resid));
+        RUN(CAS_K_GEMM_GATEUP, gemm(EPI_SWIGLU, 2, w.wgu, m.xn, 2 * ffn, c->kp_d, gu));
+        RUN(CAS_K_GEMM_DOWN, gemm(EPI_RESID, 3, w.wd, m.sw, d, c->kp_f, resid));
     }
     if (logit_rows > 0) {
         RUN(CAS_K_RMSNORM, norm(c->final_norm, T - logit_rows, logit_rows));
@@ -572,7 +591,7 @@ hipError_t enqueue_prefill(cas_ctx* c, int T, int logit_rows) {
         gh.N = f.vocab;
         gh.Kp = c->kp_d;
         gh.W = c->lm_head;
-        gh.X = c->d_xn;
+        gh.X = m.xn;
         gh.out = c->d_logits;
         gh.ldo = f.vocab;
         gh.kmaj = 1;
@@ -711,13 +730,45 @@ cas_status do_forward(cas_ctx* c, const int32_t* tokens, const int32_t* parent, 
     return CAS_OK;
 }
 
-// Prefill of n (more than 128) tokens in equal blocks of at most pf_rows rows.
+// The prefill blocks' buffers, on the context's device whatever the caller's
+// current one, allocated if they are not there yet; false where the device has no
+// room for them (the prompt then runs as tree chunks, with the same bits).
+bool prefill_buffers(cas_ctx* c) {
+    if (c->pf.rows) return true;
+    const cas_config& f = c->cfg;
+    int cur = -1;
+    if (hipGetDevice(&cur) != hipSuccess || (cur != c->dev && hipSetDevice(c->dev) != hipSuccess)) return false;
+    const size_t es = c->es, d = f.d_model;
+    const size_t ks = std::max(gemm_parts_count(c->et, f.d_model, c->kp_q, 1),
+                               gemm_parts_count(c->et, f.d_model, c->kp_f, 1));
+    // (a block of n > rows tokens has at least rows / 2 of them: more than 128)
+    for (int rows = std::min(f.max_ctx, kPrefillRows);; rows /= 2) {
+        const size_t R = rows, RT = 16 * (size_t)col_tiles(rows), RS = std::min(rows, PF_SPLIT_ROWS);
+        const size_t part[] = {R * 4, R * 4, R * 4, R * d * 4, RT * c->kp_d * es, R * c->qrows * es,
+                               RT * c->kp_q * es, RT * c->kp_f * es, ks > 1 ? ks * RS * d * 4 : 0};
+        size_t off[sizeof part / sizeof part[0]], bytes = 0;
+        for (size_t i = 0; i < sizeof part / sizeof part[0]; ++i) {
+            off[i] = bytes;
+            bytes += (part[i] + 255) / 256 * 256;
+        }
+        char* p = nullptr;
+        if ((c->chk_pf < 0 || rows <= c->chk_pf) && dalloc(c, &p, bytes) == hipSuccess) {
+            c->pf = {rows, (int*)(p + off[0]), (int*)(p + off[1]), (int*)(p + off[2]), (float*)(p + off[3]), p + off[4],
+                     p + off[5], p + off[6], p + off[7], (float*)(p + off[8])};
+            break;
+        }
+        (void)hipGetLastError();  // (the launches after it report the last error)
+        if (rows / 2 < kPrefillRowsMin) break;
+    }
+    if (cur != c->dev) (void)hipSetDevice(cur);
+    return c->pf.rows > 0;
+}
+
+// Prefill of n (more than 128) tokens in equal blocks of at most pf.rows rows.
 // Afterwards the logits are those of the last tree-sized chunk's rows, as
 // after the chunk-wise prefill of shorter prompts.
 cas_status do_prefill_rows(cas_ctx* c, const int32_t* tokens, int n) {
-    cas_status st = check_ready(c, nullptr);
-    if (st != CAS_OK) return st;
-    const int blocks = (n + c->pf_rows - 1) / c->pf_rows, last = (n - 1) % c->cfg.max_tree + 1;
+    const int blocks = (n + c->pf.rows - 1) / c->pf.rows, last = (n - 1) % c->cfg.max_tree + 1;
     c->n_nodes = 0;
     c->verified_n = 0;
     for (int b = 0; b < blocks; ++b) {
@@ -729,7 +780,7 @@ cas_status do_prefill_rows(cas_ctx* c, const int32_t* tokens, int n) {
         memcpy(buf, &sp, sizeof sp);
         memcpy(buf + 16, tokens + t0, sizeof(int32_t) * T);
         HIPCHK(c, hipMemcpyAsync(c->d_sp, buf, sizeof sp, hipMemcpyHostToDevice, c->stream));
-        HIPCHK(c, hipMemcpyAsync(c->d_ptok, buf + 16, 4 * (size_t)T, hipMemcpyHostToDevice, c->stream));
+        HIPCHK(c, hipMemcpyAsync(c->pf.tok, buf + 16, 4 * (size_t)T, hipMemcpyHostToDevice, c->stream));
         HIPCHK(c, hipEventRecord(ev, c->stream));
         const hipError_t e = enqueue_prefill(c, T, b + 1 == blocks ? last : 0);
         if (e != hipSuccess) return hip_fail(c, e, "prefill launch");
@@ -912,34 +963,29 @@ cas_status cas_create(const cas_config* cfg, int device, void* stream, cas_ctx**
             hipMemcpy(c->rope_sin, sn.data(), sn.size() * 4, hipMemcpyHostToDevice) != hipSuccess)
             return cleanup(CAS_ERR_DEVICE, "RoPE table upload");
     }
-    // rows of the activation buffers: trees and prefill blocks; the tiled ones
-    // hold whole 128-row (trees) or 256-row (prefill) column tiles
-    const size_t P = c->pf_rows = std::max(f.max_tree, std::min(f.max_ctx, kPrefillRows));
-    const size_t PT = 16 * (size_t)std::max(8, col_tiles(c->pf_rows));
-    ALLOC(c->d_ptok, P * 4);
     static_assert(sizeof(StepParams) == 16 && kStageBytes >= 16 + 8 * kRoundNodes, "one upload per forward");
     ALLOC(c->d_sp, 16 + 8 * kRoundNodes);  // step parameters, then the round's tokens and parents
     c->d_rtok = (int*)(c->d_sp + 1);
     c->d_rpar = c->d_rtok + kRoundNodes;
     ALLOC(c->d_chk, 16);
     if (hipMemset(c->d_chk, 0, 16) != hipSuccess) return cleanup(CAS_ERR_DEVICE, "hipMemset of the check word");
-    ALLOC(c->d_row_pos, P * 4);
-    ALLOC(c->d_row_slot, P * 4);
+    ALLOC(c->d_row_pos, T * 4);
+    ALLOC(c->d_row_slot, T * 4);
     ALLOC(c->d_row_anc, T * 16);
-    ALLOC(c->d_h, P * d * 4);
-    // tiled activations hold rows of the padded width
+    ALLOC(c->d_h, T * d * 4);
+    // tiled activations hold 128 rows (8 column tiles) of the padded width
     const size_t kpmax = std::max(std::max(c->kp_d, c->kp_q), c->kp_f);
     const size_t kqmax = std::max(std::max(c->kq_d, c->kq_q), c->kq_f);
-    ALLOC(c->d_xn, PT * kpmax * es);
+    ALLOC(c->d_xn, 128 * kpmax * es);
     ALLOC(c->d_xq, 128 * kqmax);
     ALLOC(c->d_xs, T * 4);
-    ALLOC(c->d_q, P * c->qrows * es);
-    ALLOC(c->d_ao, PT * (size_t)c->kp_q * es);
-    ALLOC(c->d_sw, PT * (size_t)c->kp_f * es);
+    ALLOC(c->d_q, T * c->qrows * es);
+    ALLOC(c->d_ao, 128 * (size_t)c->kp_q * es);
+    ALLOC(c->d_sw, 128 * (size_t)c->kp_f * es);
     ALLOC(c->d_logits, T * (size_t)f.vocab * 4);
     c->part_bytes = attention_work_bytes(c->ctx_cap, (int)T, f.n_heads, f.head_dim);
     ALLOC(c->d_part, c->part_bytes);
-    ALLOC(c->d_gpart, sizeof(float) * 8 * std::max((size_t)f.max_tree, std::min(P, (size_t)PF_SPLIT_ROWS)) * f.d_model);
+    ALLOC(c->d_gpart, sizeof(float) * 8 * (size_t)f.max_tree * f.d_model);
     ALLOC(c->d_gbuf, T * 8 * 3 * 4);  // per row: 8 argmax parts of (index, value, NaN flag)
     ALLOC(c->d_acc, (T + 1) * 4);
     if (hipMemset(c->d_rtok, 0, kRoundNodes * 4) != hipSuccess || hipMemset(c->d_rpar, 0xff, kRoundNodes * 4) != hipSuccess)
@@ -1096,7 +1142,11 @@ cas_status cas_prefill(cas_ctx* c, const int32_t* tokens, int32_t n) {
     if (c->Lc + n > c->cfg.max_ctx) return fail(c, CAS_ERR_CAPACITY, "prefill would exceed max_ctx");
     for (int i = 0; i < n; ++i)
         if (tokens[i] < 0 || tokens[i] >= c->cfg.vocab) return fail(c, CAS_ERR_ARG, "token out of range");
-    if (n > kPrefillTree) return do_prefill_rows(c, tokens, n);
+    if (n > kPrefillTree) {
+        const cas_status st = check_ready(c, nullptr);
+        if (st != CAS_OK) return st;
+        if (prefill_buffers(c)) return do_prefill_rows(c, tokens, n);
+    }
     std::vector<int32_t> par(c->cfg.max_tree), acc(c->cfg.max_tree);
     for (int i = 0; i < c->cfg.max_tree; ++i) {
         par[i] = i - 1;
@@ -1305,6 +1355,14 @@ cas_status cas_debug_limit_slots(cas_ctx* c, int32_t cap) {
     if (!kDeviceChecks) return fail(c, CAS_ERR_UNSUPPORTED, "device checks are compiled only into CAS_DEBUG builds");
     if (cap < 0 || cap > c->cfg.max_ctx) return fail(c, CAS_ERR_ARG, "cap must be in [0, max_ctx]");
     c->chk_cap = cap;
+    return CAS_OK;
+}
+
+cas_status cas_debug_limit_prefill(cas_ctx* c, int32_t rows) {
+    if (!c) return CAS_ERR_ARG;
+    if (!kDeviceChecks) return fail(c, CAS_ERR_UNSUPPORTED, "the limit is compiled only into CAS_DEBUG builds");
+    if (rows < -1) return fail(c, CAS_ERR_ARG, "rows must be >= -1");
+    c->chk_pf = rows;
     return CAS_OK;
 }
 

@@ -265,6 +265,7 @@ static void error_paths(cas_ctx* c, const shape_t* s) {
         CHECK(cas_debug_limit_slots(c, s->max_ctx + 1) == CAS_ERR_ARG);
     } else {
         CHECK(cas_debug_limit_slots(c, 8) == CAS_ERR_UNSUPPORTED);
+        CHECK(cas_debug_limit_prefill(c, 0) == CAS_ERR_UNSUPPORTED);
     }
 }
 

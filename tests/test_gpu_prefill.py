@@ -4,6 +4,7 @@ committed KV of every layer, the logits the prefill leaves behind and the
 next forward's logits hold the same bits, whatever the block and tile edges."""
 import numpy as np
 import pytest
+import torch  # (before the library: both then share one HIP runtime)
 
 from paper_2510_26843_amd import cas, synth
 
@@ -62,6 +63,62 @@ def test_long_prefill_matches_tree_chunks(name, head, n):
     assert np.array_equal(got.forward(tt, tree), ref.forward(tt, tree))
     ref.close()
     got.close()
+
+
+def _free():
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+
+
+def test_prefill_buffers_are_taken_by_the_first_long_prompt():
+    # the blocks' buffers of this shape are 105 MB (2048 rows, widths 1024 and
+    # 16384, eight split-K sums of 512 rows); the context's weights, their
+    # staging, the KV cache of 4096 slots and the trees' buffers 180 MB
+    shape = S("mem", 1, 1024, 8, 8, 128, 16384, 512, 1e4, 1e-6, "bf16")
+    w = synth.gen_weights(shape, seed=3)
+    prompt = synth.gen_prompt(shape.vocab, 2300, seed=1)
+    m = _model(shape, w, 4096)
+    m.prefill(prompt[:300])
+    m.close()  # (the code is loaded, and the loads' staging is gone)
+    free = _free()
+    m = _model(shape, w, 4096)
+    m.prefill(prompt[:128])
+    held = _free()
+    assert free - held < 240e6
+    m.prefill(prompt[128:300])
+    blocks = _free()
+    assert 90e6 < held - blocks < 150e6
+    m.set_committed(0)
+    m.prefill(prompt)
+    assert _free() == blocks  # kept, not taken again
+    m.close()
+    assert _free() >= held
+
+
+@pytest.mark.parametrize("name", ["f32", "gqa"])
+@pytest.mark.parametrize("rows", [0, 511, 700, 1024])
+def test_long_prefill_where_the_device_has_no_room(name, rows):
+    """Smaller blocks, or tree chunks where not even those fit: the same bits."""
+    shape = SHAPES[name]
+    w = synth.gen_weights(shape, seed=3)
+    prompt = synth.gen_prompt(shape.vocab, 2300, seed=1)
+    ms = []
+    for limit in (-1, rows):
+        m = cas.Model(shape, max_ctx=2500, max_tree=128, debug=True)
+        m.load_weights(w)
+        m.debug_limit_prefill(limit)
+        m.prefill(prompt)
+        assert m.committed == 2300 and m.debug_check() == 0
+        ms.append(m)
+    a, b = ms
+    for l in range(shape.n_layers):
+        for x, y in zip(a.kv_read(l, 2300), b.kv_read(l, 2300)):
+            assert np.array_equal(x, y)
+    n = (2300 - 1) % 128 + 1
+    for x, y in zip(a.topk(4, n), b.topk(4, n)):
+        assert np.array_equal(x, y)
+    a.close()
+    b.close()
 
 
 def test_long_prefill_refuses_what_it_refused():
