@@ -190,6 +190,15 @@ size_t cas_op_gemm_qx_work_bytes(int32_t wtype, int32_t N, int32_t K, int32_t T)
 cas_status cas_op_gemm_qx(int32_t wtype, const int8_t* W, const float* ws, const uint16_t* x, int32_t N, int32_t K,
                           int32_t T, int32_t qmax, float* parts, void* work, size_t work_bytes, void* stream);
 
+/*
+ * How a prefill block of T rows (129 to 2048) runs a linear layer; host only.
+ *   wtype:  CAS_W_F32 or CAS_W_BF16; W [N][K]
+ *   resid:  1 for the O and down projections (added to the residual stream)
+ *   info:   weight rows and activation rows of a workgroup's block, the K
+ *           ranges summed apart, and 1 if each of them has workgroups of its own
+ */
+cas_status cas_op_prefill_block(int32_t wtype, int32_t N, int32_t K, int32_t T, int32_t resid, int32_t info[4]);
+
 /* Plain device copy kernel (16-byte vector loads and stores): the reference
  * traffic for calibrating HBM byte counters.  bytes must be a multiple of 16. */
 cas_status cas_op_copy(void* dst, const void* src, size_t bytes, void* stream);

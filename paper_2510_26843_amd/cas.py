@@ -49,7 +49,7 @@ EXPORTS = ("cas_create", "cas_destroy", "cas_last_error", "cas_create_error", "c
            "cas_op_attn_merge", "cas_op_attn_merge_work_bytes", "cas_op_gemm_qx", "cas_op_gemm_qx_splits",
            "cas_op_gemm_qx_work_bytes", "cas_op_attention_noalloc", "cas_op_attention_noalloc_max_bytes",
            "cas_debug_build", "cas_debug_check", "cas_debug_limit_slots",
-           "cas_debug_limit_prefill", "cas_set_gemv")
+           "cas_debug_limit_prefill", "cas_set_gemv", "cas_op_prefill_block")
 # device check codes (cas_debug_check)
 DEVICE_CHECKS = ["none", "tree size", "token id", "parent order", "slot capacity", "RoPE position",
                  "KV write slot", "attention slots", "compaction path", "acceptance parent"]
@@ -132,6 +132,7 @@ def lib(debug: bool = False):
             "cas_debug_check": ([P, P], I),
             "cas_debug_limit_slots": ([P, I], I),
             "cas_debug_limit_prefill": ([P, I], I),
+            "cas_op_prefill_block": ([I, I, I, I, I, P], I),
         }
         for name, (args, res) in sig.items():
             fn = getattr(L, name)
@@ -448,6 +449,13 @@ def op_attn_merge(part_o, part_ml, S: int, T: int, H: int, hd: int, out=None, q=
 
 def op_gemm_qx_splits(wtype: int, N: int, K: int, T: int) -> int:
     return int(lib().cas_op_gemm_qx_splits(wtype, N, K, T))
+
+
+def op_prefill_block(wtype: int, N: int, K: int, T: int, resid: bool) -> Tuple[int, int, int, int]:
+    """(weight rows, activation rows, K ranges, ranges apart) of a prefill's linear layer."""
+    info = np.zeros(4, dtype=np.int32)
+    _ochk(lib().cas_op_prefill_block(wtype, N, K, T, int(resid), _p(info)), "cas_op_prefill_block")
+    return tuple(int(x) for x in info)
 
 
 def op_gemm_qx(wtype: int, W, ws, x, N: int, K: int, T: int, qmax: int, parts, stream=None) -> None:

@@ -215,6 +215,9 @@ int gemm_sum_ranges(int wtype, int N, int Kp, int resid);
 // residual stream, EPI_STORE (where gemm_rows_split says so) leaves each
 // range's sums at a.out + k * a.part_stride, as launch_gemm_parts does.
 hipError_t launch_gemm_rows(int wtype, int epi, const GemmArgs& a, hipStream_t s);
+// Its block (weight rows x activation rows) for ksplit K ranges in turn.
+enum RowsBlock { RB_64_64, RB_128_128, RB_128_256, RB_256_256 };
+RowsBlock gemm_rows_block(int N, int T, int ksplit);
 constexpr int PF_SPLIT_ROWS = 512;  // most rows of a prefill with split partial sums
 bool gemm_rows_split(int wtype, int N, int Kp, int T);
 

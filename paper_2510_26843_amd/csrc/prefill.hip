@@ -343,30 +343,40 @@ static hipError_t gemm_rows_launch(const GemmArgs& a, hipStream_t s) {
 // gate/up 537 / 497 / 453; 1504 rows of its down projection 188 / 172 / 273.
 // (Eight waves and not four for 128 x 128: 7B down 88 against 96 us; rings of
 // eight stages were slower, 113 us.)
-template <int WT, int EPI, typename AT, bool KM>
-static hipError_t gemm_rows_go(const GemmArgs& a, hipStream_t s) {
-    if (a.kmaj != (int)KM) return hipErrorInvalidValue;
-    const int tt = (a.T + 15) / 16, tn = a.N / 16;
+// Small matrices: up to 64 blocks of 128 x 128 would leave most CUs without
+// one, so blocks of 64 x 64 (four waves of 16 x 64).  1000 rows, 128 x 128
+// against 64 x 64 blocks: QKV of the 512-wide decoder 13.2 -> 7.7 us, its
+// down projection 16.8 -> 11.7, that of the 1024-wide one 27.2 -> 18.7,
+// QKV of the 256-wide fp32 decoder 30.6 -> 12.7.
+RowsBlock gemm_rows_block(int N, int T, int ksplit) {
+    const int tt = (T + 15) / 16, tn = N / 16;
     auto blocks = [&](int bn, int bt) { return (long)((tt + bt - 1) / bt) * ((tn + bn - 1) / bn); };
     const long n1 = blocks(8, 8), n2 = blocks(8, 16), n4 = blocks(16, 16);
     const double c1 = n1 <= 256 ? 1.2 : std::max(2.0, n1 / 256.0);
     const double c2 = 1.8 * ((n2 + 255) / 256), c4 = 3.0 * ((n4 + 255) / 256);
-    // Small matrices: up to 64 blocks of 128 x 128 would leave most CUs without
-    // one, so blocks of 64 x 64 (four waves of 16 x 64).  1000 rows, 128 x 128
-    // against 64 x 64 blocks: QKV of the 512-wide decoder 13.2 -> 7.7 us, its
-    // down projection 16.8 -> 11.7, that of the 1024-wide one 27.2 -> 18.7,
-    // QKV of the 256-wide fp32 decoder 30.6 -> 12.7.
-    if (n1 <= 64) {
-        if (a.ksplit > 1) return gemm_rows_launch<WT, 1, 4, 4, 1, EPI, AT, KM, true>(a, s);
-        return gemm_rows_launch<WT, 1, 4, 4, 1, EPI, AT, KM, false>(a, s);
+    if (n1 <= 64) return RB_64_64;
+    if (ksplit == 1 && c4 < c1 && c4 < c2) return RB_256_256;
+    return c2 < c1 ? RB_128_256 : RB_128_128;
+}
+
+template <int WT, int EPI, typename AT, bool KM, bool RNG>
+static hipError_t gemm_rows_shape(const GemmArgs& a, hipStream_t s) {
+    switch (gemm_rows_block(a.N, a.T, a.ksplit)) {
+    case RB_64_64:  // (a matrix whose K range is whole has 8192 rows or more)
+        if constexpr (RNG) return gemm_rows_launch<WT, 1, 4, 4, 1, EPI, AT, KM, true>(a, s);
+        break;
+    case RB_128_128: return gemm_rows_launch<WT, 2, 4, 4, 2, EPI, AT, KM, RNG>(a, s);
+    case RB_128_256: return gemm_rows_launch<WT, 4, 4, 2, 4, EPI, AT, KM, RNG>(a, s);
+    case RB_256_256:  // (both accumulators of a range would not fit the registers)
+        if constexpr (!RNG) return gemm_rows_launch<WT, 8, 4, 2, 4, EPI, AT, KM, false>(a, s);
+        break;
     }
-    if (a.ksplit > 1) {
-        if (c2 < c1) return gemm_rows_launch<WT, 4, 4, 2, 4, EPI, AT, KM, true>(a, s);
-        return gemm_rows_launch<WT, 2, 4, 4, 2, EPI, AT, KM, true>(a, s);
-    }
-    if (c4 < c1 && c4 < c2) return gemm_rows_launch<WT, 8, 4, 2, 4, EPI, AT, KM, false>(a, s);
-    if (c2 < c1) return gemm_rows_launch<WT, 4, 4, 2, 4, EPI, AT, KM, false>(a, s);
-    return gemm_rows_launch<WT, 2, 4, 4, 2, EPI, AT, KM, false>(a, s);
+    return hipErrorInvalidValue;
+}
+template <int WT, int EPI, typename AT, bool KM>
+static hipError_t gemm_rows_go(const GemmArgs& a, hipStream_t s) {
+    if (a.kmaj != (int)KM) return hipErrorInvalidValue;
+    return a.ksplit > 1 ? gemm_rows_shape<WT, EPI, AT, KM, true>(a, s) : gemm_rows_shape<WT, EPI, AT, KM, false>(a, s);
 }
 
 // Residual projections of few rows (up to 128 blocks of 128 x 128: 512 rows of

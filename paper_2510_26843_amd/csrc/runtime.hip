@@ -1630,6 +1630,20 @@ cas_status cas_op_attn_merge(const float* part_o, const float* part_ml, int32_t 
     return e == hipSuccess ? CAS_OK : CAS_ERR_DEVICE;
 }
 
+cas_status cas_op_prefill_block(int32_t wtype, int32_t N, int32_t K, int32_t T, int32_t resid, int32_t info[4]) {
+    if (!info || (wtype != CAS_W_F32 && wtype != CAS_W_BF16) || N < 16 || N % 16 || K < 16 || K % 16 ||
+        T <= kPrefillTree || T > kPrefillRows)
+        return CAS_ERR_ARG;
+    const int Kp = pad_k(K, wtype), ks = gemm_sum_ranges(wtype, N, Kp, resid);
+    const bool split = resid && gemm_rows_split(wtype, N, Kp, T);
+    const RowsBlock b = split ? RB_128_128 : gemm_rows_block(N, T, ks);
+    info[0] = b == RB_64_64 ? 64 : b == RB_256_256 ? 256 : 128;
+    info[1] = b == RB_64_64 ? 64 : b == RB_128_128 ? 128 : 256;
+    info[2] = ks;
+    info[3] = split;
+    return CAS_OK;
+}
+
 int32_t cas_op_gemm_qx_splits(int32_t wtype, int32_t N, int32_t K, int32_t T) {
     if ((wtype != CAS_W_I8 && wtype != CAS_W_I4) || N < 64 || K < 16 || K % 16 || T < 1) return 0;
     const int Kp = pad_k(K, ET_I8);
