@@ -120,6 +120,46 @@ def test_slot_check_reports_and_recovers():
     dbg.close()
 
 
+WIDE = synth.ModelShape("wide_hd", 1, 256, 4, 2, 128, 4416, 512, 1e4, 1e-6, "bf16")
+
+
+@pytest.mark.parametrize("shape", [TINY, GQA, WIDE], ids=["tiny_f32", "gqa_bf16", "hd128_bf16"])
+def test_prefill_blocks_check_their_slots(shape):
+    """The checks of the prefill kernels: silent on valid prompts (and the
+    release build's bits), one of the slot checks where the limit lies inside
+    the prompt, at its start, middle and last slot, and silent again after."""
+    w = synth.gen_weights(shape, seed=7)
+    rel, dbg = (cas.Model(shape, max_ctx=512, max_tree=128, debug=d) for d in (False, True))
+    prompt = synth.gen_prompt(shape.vocab, 37 + 300, seed=4)
+    for m in (rel, dbg):
+        m.load_weights(w)
+        m.prefill(prompt[:37])
+        m.prefill(prompt[37:])
+    assert dbg.debug_check() == 0
+
+    def same():
+        for l in range(shape.n_layers):
+            for x, y in zip(rel.kv_read(l, 337), dbg.kv_read(l, 337)):
+                assert np.array_equal(x, y)
+        for x, y in zip(rel.topk(4, 300 % 128), dbg.topk(4, 300 % 128)):
+            assert np.array_equal(x, y)
+
+    same()
+    for cap in (38, 200, 336):
+        dbg.set_committed(37)
+        dbg.debug_limit_slots(cap)  # every access stays inside the real 512 slots
+        dbg.prefill(prompt[37:])
+        code = dbg.debug_check()
+        assert code in SLOT_CHECKS, (cap, code)
+        dbg.debug_limit_slots(0)
+        dbg.set_committed(37)
+        dbg.prefill(prompt[37:])
+        assert dbg.debug_check() == 0
+        same()
+    rel.close()
+    dbg.close()
+
+
 def test_profile_switch_prints_kernel_table(monkeypatch, capsys):
     monkeypatch.setenv("CAS_PROFILE", "1")
     w = synth.gen_weights(TINY, seed=1)
