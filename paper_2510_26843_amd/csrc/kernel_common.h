@@ -41,15 +41,7 @@ __device__ __forceinline__ float wave_max(float v) {
     for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
     return v;
 }
-// Block-wide reductions for 256 threads; fixed combination order.
-__device__ __forceinline__ float block_sum256(float v, float* sh) {
-    v = wave_sum(v);
-    const int w = threadIdx.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[w] = v;
-    __syncthreads();
-    return ((sh[0] + sh[1]) + sh[2]) + sh[3];
-}
+// Block-wide maximum for 256 threads.
 __device__ __forceinline__ float block_max256(float v, float* sh) {
     v = wave_max(v);
     const int w = threadIdx.x >> 6;

@@ -171,7 +171,8 @@ __global__ void __launch_bounds__(64 * WN * WT_, 2) k_gemm_rows(GemmArgs a) {
     constexpr int LA = BN / W, LB = BT / W, LD = LA + LB;  // 1 KB loads per wave and step
     constexpr int SB = (BN + BT) * 1024;                   // bytes of a stage
     static_assert(!is_int<WT>() && !(RNG && SPL), "fp32 and bf16 weights; one way with the ranges");
-    static_assert(LA * W == BN && LB * W == BT && D % FRAG_U == 0, "stage shape");
+    static_assert(LA * W == BN && LB * W == BT, "stage shape");
+    static_assert(D == FRAG_U, "a round of the ring is a chunk, so that no step is past the last");
     constexpr bool BFX = sizeof(AT) == 2 && (EPI == EPI_SWIGLU || EPI == EPI_QKV);  // the 16-byte epilogues
     static_assert(!BFX || (TW == 4 && 2 * W * EP_LDS <= D * SB), "epilogue shape");
     __shared__ __attribute__((aligned(16))) char sm[D * SB];
@@ -253,7 +254,6 @@ __global__ void __launch_bounds__(64 * WN * WT_, 2) k_gemm_rows(GemmArgs a) {
 #pragma unroll
         for (int q = 0; q < D; ++q) {
             const int s = s0 + q, p = q & 1;
-            if (D > FRAG_U && q % FRAG_U == 0 && s >= NS) break;
             // stage q is read by every wave, stage q + 1 has landed
             stage_wait<(D - 2) * LD>();
             load(q, s + D + 1 < NS);
