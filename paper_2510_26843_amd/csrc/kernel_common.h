@@ -252,12 +252,14 @@ __device__ __forceinline__ void st2(float* p, size_t o, float x, float y) { *(fl
 
 // Epilogue of one 16-row weight tile: lane holds y[n = 16*tile + 4g + i][t = row0 + 16j + r].
 // qp: the tile's preloaded QKV operands (EPI_QKV only).  TPW: tiles per wave.
-template <int WT, int NT, int EPI, typename AT, int TPW = 1>
+// ROWS: a prefill's rows (row_tiles).
+template <int WT, int NT, int EPI, typename AT, int TPW = 1, bool ROWS = false>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, const typename WTr<WT>::acc_t (&acc)[NT], int tile,
                                               int last_tile, int lane, const QkvPre<NT>& qp, int row0 = 0) {
     const int r = lane & 15, g = lane >> 4, T = a.T;
     const int nb = tile * 16 + 4 * g;
-    const int nto = col_tiles(T);  // column tiles of a tiled output (NT, or 1 held for a wider layout)
+    // column tiles of a tiled output (NT, or 1 held for a wider layout)
+    const int nto = ROWS ? row_tiles(T) : col_tiles(T);
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
         const int t = row0 + 16 * j + r;
@@ -338,7 +340,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, const typename 
         if (tile == last_tile) {
             const int kp = (a.out_k + 16 * EO - 1) / (16 * EO) * (16 * EO);
             const int w = kp - a.out_k;
-            const int rows = min(T - row0, 16 * NT);
+            const int rows = ROWS ? min(T - row0, 16 * NT) : T;
             for (int idx = lane; idx < rows * w; idx += 64)
                 Act<AT>::st((AT*)a.out, xt_off(row0 + idx / w, a.out_k + idx % w, nto, EO), 0.f);
         }

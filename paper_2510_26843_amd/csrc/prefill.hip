@@ -85,7 +85,7 @@ __device__ __forceinline__ void rows_epilogue(const GemmArgs& a, const f32x4 (&v
         for (int j = 0; j < 4; ++j)
             w[j] = pack_bf(v[j][0] / (1.0f + expf(-v[j][0])) * v[j][1], v[j][2] / (1.0f + expf(-v[j][2])) * v[j][3]);
         lane_transpose4(w);
-        const int nto = col_tiles(T);
+        const int nto = row_tiles(T);
         if (t < T) *(uint4*)((uint16_t*)a.out + xt_off(t, tile * 8, nto, 8)) = make_uint4(w[0], w[1], w[2], w[3]);
         if (tile == last_tile) {  // and the pad columns
             const int pad = (a.out_k + 127) / 128 * 128 - a.out_k, rows = min(T - row0, 64);
@@ -179,7 +179,7 @@ __global__ void __launch_bounds__(64 * WN * WT_, 2) k_gemm_rows(GemmArgs a) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wn = wave / WT_, wt = wave % WT_;
-    const int ntiles = a.N >> 4, nto = col_tiles(a.T);
+    const int ntiles = a.N >> 4, nto = row_tiles(a.T);
     // Workgroups go to the XCDs round robin; each XCD takes a run of
     // consecutive (weight block, row block) pairs, rows fastest, so that the
     // workgroups sharing a weight block share an L2.
@@ -310,8 +310,8 @@ __global__ void __launch_bounds__(64 * WN * WT_, 2) k_gemm_rows(GemmArgs a) {
             if (tile0 + i >= ntiles) continue;
             QkvPre<TW> qp;
             if constexpr (EPI == EPI_QKV) qp.load(a, tile0 + i, lane, row0);
-            if constexpr (RNG) gemm_epilogue<WT, TW, EPI, AT>(a, tot[i], tile0 + i, ntiles - 1, lane, qp, row0);
-            else gemm_epilogue<WT, TW, EPI, AT>(a, acc[i], tile0 + i, ntiles - 1, lane, qp, row0);
+            if constexpr (RNG) gemm_epilogue<WT, TW, EPI, AT, 1, true>(a, tot[i], tile0 + i, ntiles - 1, lane, qp, row0);
+            else gemm_epilogue<WT, TW, EPI, AT, 1, true>(a, acc[i], tile0 + i, ntiles - 1, lane, qp, row0);
         }
     }
 }
@@ -546,7 +546,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_causal(const AttnArgs a, float 
     const int t = t0 + r;
     if (t < T) {
         const float inv = L > 0.f ? 1.f / L : 0.f;
-        const int nto = col_tiles(T);
+        const int nto = row_tiles(T);
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt)
             st4((uint16_t*)a.out, xt_off(t, head * HD + 16 * dt + 4 * g, nto, 8), acc[dt][0] * inv, acc[dt][1] * inv,

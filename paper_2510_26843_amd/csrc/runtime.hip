@@ -743,7 +743,7 @@ bool prefill_buffers(cas_ctx* c) {
                                gemm_parts_count(c->et, f.d_model, c->kp_f, 1));
     // (a block of n > rows tokens has at least rows / 2 of them: more than 128)
     for (int rows = std::min(f.max_ctx, kPrefillRows);; rows /= 2) {
-        const size_t R = rows, RT = 16 * (size_t)col_tiles(rows), RS = std::min(rows, PF_SPLIT_ROWS);
+        const size_t R = rows, RT = 16 * (size_t)row_tiles(rows), RS = std::min(rows, PF_SPLIT_ROWS);
         const size_t part[] = {R * 4, R * 4, R * 4, R * d * 4, RT * c->kp_d * es, R * c->qrows * es,
                                RT * c->kp_q * es, RT * c->kp_f * es, ks > 1 ? ks * RS * d * 4 : 0};
         size_t off[sizeof part / sizeof part[0]], bytes = 0;
