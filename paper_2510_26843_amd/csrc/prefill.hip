@@ -266,7 +266,8 @@ __global__ void __launch_bounds__(64 * WN * WT_, 2) k_gemm_rows(GemmArgs a) {
             if constexpr (NW * TW == 32) {
                 // two MFMAs per LDS read (left to itself the compiler puts the
                 // reads in front): 256 x 256 blocks 201 -> 193 us for the 7B
-                // gate/up at 1024 rows; 128 x 128 blocks were slower this way
+                // gate/up at 1024 rows in a copy of the loop that only stores;
+                // 128 x 128 blocks were slower this way
 #pragma unroll
                 for (int k = 0; k < NW + TW; ++k) {
                     __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
@@ -335,14 +336,20 @@ static hipError_t gemm_rows_launch(const GemmArgs& a, hipStream_t s) {
 
 // Blocks of 128 x 128 as eight waves of 32 x 64 (64 KB: two workgroups per CU),
 // 128 x 256 as eight of 64 x 64, or 256 x 256 as eight of 128 x 64.  The larger
-// ones read less LDS per MFMA but come one per CU: measured at K = 4096, a CU's
-// first 128 x 128 block takes 40 us and each further one 32-36, a round of
-// 128 x 256 blocks 57-65 us, one of 256 x 256 blocks 90-105.  The block with
-// the least cost in these units is taken: 1024 rows of the 7B QKV 95 / 115 /
-// 101 us, gate/up 200 / 194 / 201, down 88 / 130 / 206; 2048 rows of the 8B
-// gate/up 537 / 497 / 453; 1504 rows of its down projection 188 / 172 / 273.
-// (Eight waves and not four for 128 x 128: 7B down 88 against 96 us; rings of
-// eight stages were slower, 113 us.)
+// ones read less LDS per MFMA but come one per CU: in a copy of the loop that
+// only stores its sums, at K = 4096, a CU's first 128 x 128 block took 40 us and
+// each further one 32-36, a round of 128 x 256 blocks 57-65 us, one of 256 x 256
+// blocks 90-105.  The block with the least cost in these units is taken, at
+// every K.  These kernels in a prefill, by events, the three blocks in turn
+// (* the rule's):
+//   QKV      7B 1024 rows *108 / 123 / 102 us, 2048 rows 207 / *198 / 208;
+//            13B 1024 168 / 152 / *135; 8B (K ranges) 1504 *98 / 120
+//   gate/up  7B 512 rows 100 / 111 / *86, 1024 *182 / 166 / 182, 2048 340 / 334 /
+//            *286; 13B 1024 268 / 270 / *229; 8B 2048 436 / 396 / *380
+//   down     7B 1024 *101 / 138, 2048 186 / *159; 8B 1504 225 / *184
+// The rule misses the best one at 1024 rows of 7B (QKV by 6%, gate/up by 9%).
+// (In the same copy of the loop, the 7B down projection: 128 x 128 as eight
+// waves 88 us, as four 96; rings of eight stages 113.)
 // Small matrices: up to 64 blocks of 128 x 128 would leave most CUs without
 // one, so blocks of 64 x 64 (four waves of 16 x 64).  1000 rows, 128 x 128
 // against 64 x 64 blocks: QKV of the 512-wide decoder 13.2 -> 7.7 us, its
@@ -429,11 +436,12 @@ __device__ __forceinline__ void lds_load16_b(const void* src, void* dst) {
 // exactly as k_attn_merge does, in split order: the same bits as a forward of
 // up to 128 rows, without the partials' trip through memory.  Parts wholly
 // past a tile's last row would add zero and are left out.
-// The VALU work of the softmax bounds it (some 1200 instructions against 192
-// MFMAs per wave and split).  Two workgroups of 64 rows per CU even out the
-// rows' unequal walks: eight waves on 128 KB of whole K and V stages, one
-// workgroup per CU, took 38 us per layer for 1024 tokens of the 7B shape and
-// 93 for 1501 of 8B (after 1500); these take 32 and 86.
+// Most of what it issues is the softmax: by counters 1280 VALU instructions
+// against 192 MFMAs per wave and split, and the matrix cores are 15% busy (7B,
+// 1024 tokens).  Two workgroups of 64 rows per CU even out the rows' unequal
+// walks: eight waves on 128 KB of whole K and V stages, one workgroup per CU,
+// took 38 us per layer for 1024 tokens of the 7B shape and 93 for 1501 of 8B
+// (after 1500); these take 32 and 86.
 template <int HD>
 __global__ void __launch_bounds__(256, 2) k_attn_causal(const AttnArgs a, float scale_log2) {
     constexpr int UD = HD / 32, DG = HD / 4, NDT = HD / 16, TE = 32 * HD, QW = 4;
