@@ -3,6 +3,7 @@ chunk by chunk through the verify forward (a chain of up to 128 nodes): the
 committed KV of every layer, the logits the prefill leaves behind and the
 next forward's logits hold the same bits, whatever the block and tile edges."""
 import dataclasses
+import gc
 
 import numpy as np
 import pytest
@@ -103,6 +104,7 @@ def test_long_prefill_matches_tree_chunks(name, head, n):
 
 
 def _free():
+    gc.collect()  # (contexts that other tests left open)
     torch.cuda.synchronize()
     return torch.cuda.mem_get_info()[0]
 
